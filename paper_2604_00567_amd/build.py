@@ -22,6 +22,10 @@ LIB = os.path.join(HERE, "libdsfft.so")
 HIP_SOURCES = ["api.cpp", "batch.cpp", "serve.cpp", "serve_loop.cpp", "tune.cpp", "scratch.cpp", "kernels_f16.hip", "kernels_f32.hip",
                "kernels_f16f32.hip", "kernels_batch.hip"]
 CXX_SOURCES = ["tables.cpp"]
+# The kernel files hold every configuration of a precision; they are compiled
+# in parts (kParts in kernels.hpp), which run side by side.
+PARTED = ["kernels_f16.hip", "kernels_f32.hip", "kernels_f16f32.hip"]
+PARTS = 3
 
 ARCH = os.environ.get("DSFFT_ARCH", "gfx950")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
@@ -37,11 +41,12 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def _compile(src: str) -> str:
+def _compile(src: str, part: int | None = None) -> str:
     path = os.path.join(CSRC, src)
-    obj = os.path.join(OUT_DIR, os.path.splitext(src)[0] + ".o")
+    obj = os.path.join(OUT_DIR, os.path.splitext(src)[0] + ("" if part is None else f"_{part}") + ".o")
     if src in HIP_SOURCES:
-        cmd = [_hipcc(), "-x", "hip"] + COMMON + HIP_FLAGS + ["-c", path, "-o", obj]
+        define = [] if part is None else [f"-DKERNEL_PART={part}"]
+        cmd = [_hipcc(), "-x", "hip"] + COMMON + HIP_FLAGS + define + ["-c", path, "-o", obj]
     else:
         cmd = [_hipcc()] + COMMON + ["-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -52,9 +57,10 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
-    srcs = HIP_SOURCES + CXX_SOURCES
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
+    jobs = [(s, p) for s in PARTED for p in range(PARTS)]
+    jobs += [(s, None) for s in HIP_SOURCES + CXX_SOURCES if s not in PARTED]
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
+        objs = list(ex.map(lambda j: _compile(*j), jobs))
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

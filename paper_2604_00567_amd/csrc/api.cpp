@@ -63,6 +63,7 @@ int get_table(int64_t n, int dtype, int kind, bool inverse, std::shared_ptr<Devi
     auto t = std::make_shared<DeviceTable>();
     t->ncap = ncap;
     t->bytes = img.size();
+    t->quarter = radix == 2 && quarter_symmetric(img, ncap, dtype, inverse);
     e = hipMalloc(&t->ptr, img.size());
     if (e != hipSuccess) {
         t->ptr = nullptr;
@@ -84,9 +85,28 @@ int get_table(int64_t n, int dtype, int kind, bool inverse, std::shared_ptr<Devi
 
 // ------------------------------------------------------------ kernel choice
 
+// All configurations of one dtype, in order of preference per (mode, log_nu),
+// from the parts they were compiled in.
+static std::vector<KernelCfg> merge_parts(const KernelCfg* (*const parts[kParts])(int*)) {
+    int cnt = 0;
+    const KernelCfg* t = parts[0](&cnt);
+    std::vector<KernelCfg> all(t, t + cnt);
+    for (int p = 1; p < kParts; ++p) {
+        t = parts[p](&cnt);
+        for (int i = 0; i < cnt; ++i)
+            if (t[i].mode != -1) all[i] = t[i];
+    }
+    return all;
+}
 static const KernelCfg* table_for(int dtype, int* count) {
-    return dtype == DT_F16 ? kernel_table_f16(count)
-                           : (dtype == DT_F32 ? kernel_table_f32(count) : kernel_table_f16f32(count));
+    typedef const KernelCfg* (*PartFn)(int*);
+    static const PartFn f16[kParts] = {kernel_table_f16<0>, kernel_table_f16<1>, kernel_table_f16<2>};
+    static const PartFn f32[kParts] = {kernel_table_f32<0>, kernel_table_f32<1>, kernel_table_f32<2>};
+    static const PartFn f16f32[kParts] = {kernel_table_f16f32<0>, kernel_table_f16f32<1>, kernel_table_f16f32<2>};
+    static const std::vector<KernelCfg> tables[3] = {merge_parts(f16), merge_parts(f32), merge_parts(f16f32)};
+    const std::vector<KernelCfg>& t = tables[dtype == DT_F16 ? 0 : (dtype == DT_F32 ? 1 : 2)];
+    *count = (int)t.size();
+    return t.data();
 }
 
 const KernelCfg* find_kernel(int dtype, int mode, int log_nu, int variant, bool radix4) {
@@ -109,6 +129,14 @@ const KernelCfg* find_plain_kernel(int dtype, int mode, int log_nu, bool radix4 
         const KernelCfg* k = find_kernel(dtype, mode, log_nu, v, radix4);
         if (!k || !k->staged) return k;
     }
+}
+
+// The launch of configuration k for a plan: the form that takes the second
+// quarter of each stage's twiddles from the first wherever the plan's table
+// holds that symmetry (dual-select tables) and the form is compiled.
+static LaunchFn plan_launch(const fft_plan* p, const KernelCfg* k) {
+    const LaunchFn q = p->inverse ? k->launch_quarter_inverse : k->launch_quarter;
+    return p->table->quarter && q ? q : k->launch;
 }
 
 int count_kernels(int dtype, int mode, int log_nu, bool radix4) {
@@ -221,19 +249,20 @@ int launch_plan_ws(const fft_plan* p, const void* in, void* out, hipStream_t s, 
     if (!p->k2) {
         const bool aligned16 = (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
         const KernelCfg* k = (p->k1->staged && !aligned16) ? p->k1_plain : p->k1;
-        hipError_t e = k->launch(in, out, lt, p->batch, 0, s);
+        hipError_t e = plan_launch(p, k)(in, out, lt, p->batch, 0, s);
         if (e != hipSuccess) return hip_error(e, "launch");
         return FFT_OK;
     }
+    const LaunchFn cols = plan_launch(p, p->k1), rows = plan_launch(p, p->k2);
     const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
     const size_t eb = (size_t)elem_bytes(p->dtype);
     for (int64_t b0 = 0; b0 < p->batch; b0 += chunk) {
         const int64_t nb = std::min<int64_t>(chunk, p->batch - b0);
         const char* src = (const char*)in + (size_t)b0 * p->n * eb;
         char* dst = (char*)out + (size_t)b0 * p->n * eb;
-        hipError_t e = p->k1->launch(src, ws, lt, nb << m2, m2, s);
+        hipError_t e = cols(src, ws, lt, nb << m2, m2, s);
         if (e != hipSuccess) return hip_error(e, "launch(cols)");
-        e = p->k2->launch(ws, dst, lt, nb << m1, m1, s);
+        e = rows(ws, dst, lt, nb << m1, m1, s);
         if (e != hipSuccess) return hip_error(e, "launch(rows)");
     }
     return FFT_OK;

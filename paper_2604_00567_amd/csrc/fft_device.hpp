@@ -130,11 +130,25 @@ __device__ __forceinline__ void bfly_stored(uint32_t a, uint32_t b, const TwF tw
 //               generality), whose butterflies combine four inputs with 22
 //               FMAs and read radix-4 table entries (Tw4H / Tw4F); a
 //               different canonical order, so results differ from radix 2.
-enum { ENC_TABLE = 0, ENC_SELECT = 1, ENC_BRANCH = 2, ENC_RADIX4 = 3 };
+//   ENC_QUARTER, ENC_QUARTER_INV  the table encoding, where the second quarter
+//               of each level's entries is taken from the first (bfly_quarter,
+//               forward and inverse tables): about half of the entries are
+//               loaded.  Needs a table that holds the quarter symmetry
+//               (dual-select tables do; checked when a table is built).
+//               What bounds whole transforms of 2^12 points and more beside
+//               HBM are the last pass's loads of one entry per lane and
+//               butterfly column (8 or 16 bytes each; without them binary16
+//               2^15 runs in 102 us where it takes 132): 256 MiB batches,
+//               every entry loaded against this form, binary16 2^12 5790 ->
+//               6003, 2^13 5212 -> 5765, 2^14 4724 -> 5375, 2^15 3811 -> 4705,
+//               2^16 3309 -> 3593 GB/s; binary32 2^14 4461 -> 4788; binary16
+//               storage with binary32 butterflies 2^10 4443 -> 5063 GB/s.
+enum { ENC_TABLE = 0, ENC_SELECT = 1, ENC_BRANCH = 2, ENC_RADIX4 = 3, ENC_QUARTER = 4, ENC_QUARTER_INV = 5 };
+constexpr bool is_quarter(int enc) { return enc == ENC_QUARTER || enc == ENC_QUARTER_INV; }
 
 template <int ENC>
 __device__ __forceinline__ void bfly_enc(uint32_t& a, uint32_t& b, const TwH tw) {
-    if constexpr (ENC == ENC_TABLE) {
+    if constexpr (ENC == ENC_TABLE || is_quarter(ENC)) {
         bfly(a, b, tw);
     } else {
         const bool sine = (tw.ts & 16u) != 0;      // the path flag
@@ -180,6 +194,82 @@ __device__ __forceinline__ void bfly_enc(uint32_t& a, uint32_t& b, const TwH tw)
 template <int ENC>
 __device__ __forceinline__ void bfly_enc(f2_t& a, f2_t& b, const TwF tw) {
     bfly(a, b, tw);
+}
+
+// Butterflies of the second quarter of a level from the entry of the first.
+// The twiddle a quarter turn on, W' = W_L^(j + L/4) = -j W_L^j (inverse tables:
+// +j W_L^j), lies on the other path with t' = -t and (sigma' m', m') =
+// (m, -sigma m) (inverse: (-m, sigma m)).  On the other path the operand order
+// c' is c with its halves swapped, so
+//   s' = (c'.lo - t' c'.hi, t' c'.lo + c'.hi) = (s.hi, s.lo),
+//   A' = a + (s.hi m, -s.lo sigma m),  B' = a - (s.hi m, -s.lo sigma m)
+// (inverse: A' and B' change places): the same FMAs on the same operands as
+// with the entry of W' itself, whose swaps and signs are operand modifiers.
+// Dual-select tables hold that relation bit for bit in both precisions at every
+// j but 0, where the ratios of W^0 and W^(L/4) are a zero and cot(pi/2) as FP64
+// evaluates it, the same two values at every level: the caller corrects t there
+// (quarter_fix).
+template <bool INV>
+__device__ __forceinline__ void bfly_quarter(uint32_t& a, uint32_t& b, const TwH tw) {
+    const h2_t cv = as_h2(__builtin_amdgcn_alignbit(b, b, tw.ts));
+    const h2_t tv = as_h2(tw.ts);
+    const h2_t w = as_h2(tw.w);
+    const h2_t av = as_h2(a);
+    h2_t tt, wq;
+    tt.x = -tv.y;
+    tt.y = tv.y;
+    wq.x = w.y;
+    wq.y = -w.x;
+    const h2_t s = __builtin_elementwise_fma(tt, cv.yx, cv);
+    const h2_t P = __builtin_elementwise_fma(s.yx, wq, av);
+    const h2_t Q = __builtin_elementwise_fma(-s.yx, wq, av);
+    a = as_u32(INV ? Q : P);
+    b = as_u32(INV ? P : Q);
+}
+template <bool INV>
+__device__ __forceinline__ void bfly_quarter(f2_t& a, f2_t& b, const TwF tw) {
+    const float bxf = b.x, byf = b.y;
+    const uint32_t br = __builtin_bit_cast(uint32_t, bxf);
+    const uint32_t bi = __builtin_bit_cast(uint32_t, byf);
+    const float cr = __builtin_bit_cast(float, (tw.mask & bi) | (~tw.mask & br));
+    const float ci = __builtin_bit_cast(float, (tw.mask & br) | (~tw.mask & bi));
+    const float s1 = __builtin_fmaf(-tw.t, ci, cr);
+    const float s2 = __builtin_fmaf(tw.t, cr, ci);
+    f2_t P, Q;
+    P.x = __builtin_fmaf(s2, tw.m, a.x);
+    P.y = __builtin_fmaf(-s1, tw.sm, a.y);
+    Q.x = __builtin_fmaf(-s2, tw.m, a.x);
+    Q.y = __builtin_fmaf(s1, tw.sm, a.y);
+    a = INV ? Q : P;
+    b = INV ? P : Q;
+}
+
+// The bits of t that differ between the entry of W^0 and the one that stands
+// for W^(L/4) (ratio -t(W^(L/4))), taken from level 4 (entries 2 and 3; the
+// same at every level): t ^= fix turns the first into the second.
+__device__ __forceinline__ uint32_t quarter_fix_bits(const TwH* __restrict__ lt) {
+    return (lt[2].ts ^ lt[3].ts ^ 0x80000000u) & 0xffff0000u;
+}
+__device__ __forceinline__ uint32_t quarter_fix_bits(const TwF* __restrict__ lt) {
+    const float t0 = lt[2].t, t1 = lt[3].t;
+    return __builtin_bit_cast(uint32_t, t0) ^ __builtin_bit_cast(uint32_t, t1) ^ 0x80000000u;
+}
+__device__ __forceinline__ TwH quarter_fix(TwH tw, uint32_t fix) {
+    tw.ts ^= fix;
+    return tw;
+}
+__device__ __forceinline__ TwF quarter_fix(TwF tw, uint32_t fix) {
+    const float t = tw.t;
+    tw.t = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t) ^ fix);
+    return tw;
+}
+// Whether entry c = 2^(t-1) + e of a register pass is loaded: with quarter
+// symmetry only those of each stage's first quarter (e < 2^(t-2)).
+constexpr bool quarter_loads(int enc, int c) {
+    if (!is_quarter(enc) || c < 2) return true;
+    int top = 1;
+    while (2 * top <= c) top *= 2;
+    return (c & (top / 2)) == 0;
 }
 
 template <class E> struct TwOf;
@@ -468,8 +558,10 @@ __device__ __forceinline__ void reg_pass4(E* v, const TW* tw) {
 }
 
 // T0 > 1: stages before T0 are done already (a binary16-storage first pass).
+// fix: with quarter symmetry, the correction of t in the butterfly that takes
+// entry 0 of its stage for W^(L/4): quarter_fix_bits in column 0, else 0.
 template <int LR, int ENC = ENC_TABLE, bool ODD = false, int T0 = 1, class E, class TW>
-__device__ __forceinline__ void reg_pass(E* v, const TW* tw) {
+__device__ __forceinline__ void reg_pass(E* v, const TW* tw, uint32_t fix = 0) {
     if constexpr (ENC == ENC_RADIX4) {
         static_assert(T0 == 1, "radix-4 passes start at their first stage");
         reg_pass4<LR, ODD>(v, tw);
@@ -485,7 +577,17 @@ __device__ __forceinline__ void reg_pass(E* v, const TW* tw) {
                 for (int i = 0; i < H; ++i) {
                     E a = v[i + 2 * H * e];
                     E b = v[i + H + 2 * H * e];
-                    bfly_enc<ENC>(a, b, tw[(1 << (t - 1)) + e]);
+                    const int c = (1 << (t - 1)) + e;
+                    if constexpr (is_quarter(ENC)) {
+                        const int q4 = (1 << t) >> 2;    // entries of a quarter of the span
+                        if (t > 1 && e >= q4)
+                            bfly_quarter<ENC == ENC_QUARTER_INV>(
+                                a, b, e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
+                        else
+                            bfly(a, b, tw[c]);
+                    } else {
+                        bfly_enc<ENC>(a, b, tw[c]);
+                    }
                     nv[i + H * e] = a;
                     nv[i + H * e + R / 2] = b;
                 }
@@ -896,12 +998,14 @@ __device__ __forceinline__ void group_twiddles(TwT<E, ENC>* tw, const TwT<E, ENC
         // cache, which keeps them off the vector memory path.
         const int qs = __builtin_amdgcn_readfirstlane(q);
 #pragma unroll
-        for (int c = C0 > 0 ? C0 : 1; c < C1; ++c) tw[c] = lt[qs + L0 * c];
+        for (int c = C0 > 0 ? C0 : 1; c < C1; ++c)
+            if (quarter_loads(ENC, c)) tw[c] = lt[qs + L0 * c];
     } else {
         const int qg = geo0.q0 + (q << geo0.log_lb);
         const int lg0 = L0 << geo0.log_lb;
 #pragma unroll
-        for (int c = C0 > 0 ? C0 : 1; c < C1; ++c) tw[c] = lt[qg + lg0 * c];
+        for (int c = C0 > 0 ? C0 : 1; c < C1; ++c)
+            if (quarter_loads(ENC, c)) tw[c] = lt[qg + lg0 * c];
     }
 }
 template <class E, int LOG_NU, int LOG_E, int MODE, int LR0, int LR1, int LR2, int LANE, int P,
@@ -1019,7 +1123,8 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
         // pairs for its first stage (bfly_stored), which widens them inside
         // its FMAs
         constexpr bool STORED0 = P == 0 && !PRE && !STG && std::is_same_v<E, f2_t> &&
-                                 std::is_same_v<SI, uint32_t> && Geo::kEncoding == ENC_TABLE;
+                                 std::is_same_v<SI, uint32_t> &&
+                                 (Geo::kEncoding == ENC_TABLE || is_quarter(Geo::kEncoding));
         uint32_t raw[STORED0 ? (UPL << LOG_E) : 1];
 
         // ---- gather
@@ -1067,13 +1172,22 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
             }
         }
 
+        // Quarter symmetry serves the passes whose entries depend on the lane; a
+        // first pass with its own table offsets reads the same few entries on
+        // every lane (scalar loads).
+        constexpr int PENC = is_quarter(Geo::kEncoding) && P == 0 && MODE != MODE_ROWS ? (int)ENC_TABLE
+                                                                                      : Geo::kEncoding;
+        uint32_t fix_bits = 0;
+        if constexpr (is_quarter(PENC)) fix_bits = quarter_fix_bits(lt);
+
         // ---- twiddles (once per group position) and stages (for each unit)
 #pragma unroll
         for (int u = 0; u < GPL; ++u) {
             TW tw[R];
             if constexpr (PFU) {
 #pragma unroll
-                for (int c = 1; c < R; ++c) tw[c] = twp[u * R + c];
+                for (int c = 1; c < R; ++c)
+                    if (quarter_loads(PENC, c)) tw[c] = twp[u * R + c];
             } else if constexpr (TWL) {
                 // entry q + L0 c of the table sits at q + L0 c - L0_1 of the copy
                 constexpr int L01 = 1 << PP::log_l0(1);
@@ -1081,21 +1195,28 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
                 const int q = (g + G * u) >> LOGM;
 #pragma unroll
-                for (int c = 1; c < R; ++c) tw[c] = ltw[q + L0 * c - L01];
+                for (int c = 1; c < R; ++c)
+                    if (quarter_loads(PENC, c)) tw[c] = ltw[q + L0 * c - L01];
             } else if constexpr (P == 0 && MODE == MODE_ROWS && Geo::kTwiddleLds == 3) {
                 const TW* ltw = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) +
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
 #pragma unroll
-                for (int c = 1; c < R; ++c) tw[c] = ltw[(c - 1) * UPW + ul0];
+                for (int c = 1; c < R; ++c)
+                    if (quarter_loads(PENC, c)) tw[c] = ltw[(c - 1) * UPW + ul0];
             } else if constexpr (TWX) {
                 const TW* ltp = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) -
                                                             (size_t)TPX * sizeof(TW));
                 const int q = (g + G * u) >> LOGM;
 #pragma unroll
-                for (int c = 1; c < R; ++c) tw[c] = ltp[q + L0 * c];
+                for (int c = 1; c < R; ++c)
+                    if (quarter_loads(PENC, c)) tw[c] = ltp[q + L0 * c];
             } else {
-                group_twiddles<E, LOG_NU, LOG_E, MODE, LR0, LR1, LR2, LANE, P, Geo::kEncoding>(tw, lt, geo0, g, u);
+                group_twiddles<E, LOG_NU, LOG_E, MODE, LR0, LR1, LR2, LANE, P, PENC>(tw, lt, geo0, g, u);
             }
+            // column 0 of the transform: the one whose stages pair W^0 with W^(L/4)
+            uint32_t fix = 0;
+            if (is_quarter(PENC) && ((G * u) >> LOGM) == 0)
+                fix = ((g + G * u) >> LOGM) + geo0.q0 == 0 ? fix_bits : 0;
             // radix-4 form: the first pass of an odd log2 N starts with the span-2 stage
             constexpr bool ODD = Geo::kEncoding == ENC_RADIX4 && P == 0 && (LOG_NU & 1);
             if constexpr (STORED0) {
@@ -1106,18 +1227,20 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                     const uint32_t* rg = raw + k * EL + u * R;
 #pragma unroll
                     for (int i = 0; i < R / 2; ++i) bfly_stored(rg[i], rg[i + R / 2], tw[1], vg[i], vg[i + R / 2]);
-                    reg_pass<LR, Geo::kEncoding, ODD, 2>(vg, tw);
+                    reg_pass<LR, PENC, ODD, 2>(vg, tw, fix);
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < UPL; ++k) reg_pass<LR, Geo::kEncoding, ODD>(v + k * EL + u * R, tw);
+                for (int k = 0; k < UPL; ++k) reg_pass<LR, PENC, ODD>(v + k * EL + u * R, tw, fix);
             }
         }
         if constexpr (PFN) {
             // entries c >= 1 of each group are the loaded ones
 #pragma unroll
-            for (int i = 0; i < NEXT_TW; ++i)
-                if (i & ((1 << PP::lr(P + 1)) - 1)) pin_twiddle(twn[i]);
+            for (int i = 0; i < NEXT_TW; ++i) {
+                const int c = i & ((1 << PP::lr(P + 1)) - 1);
+                if (c && quarter_loads(Geo::kEncoding, c)) pin_twiddle(twn[i]);
+            }
         }
 
         // ---- scatter

@@ -23,16 +23,31 @@ struct KernelCfg {
     int lane_tail;  // 1: the last two stages run across lanes (permlane swaps)
     int pipelined;  // 1: persistent workgroups prefetch the next block into registers;
                     // 2: each pass loads the next pass's twiddles
-    int encoding;   // path encoding of the butterfly: 0 table, 1 select, 2 branch
+    int encoding;   // path encoding of the butterfly (ENC_*)
     int threads;    // workgroup size
     size_t lds_bytes;
     LaunchFn launch;
+    // the same results from about half of the twiddle loads, for tables with
+    // quarter symmetry: forward and inverse (null where not compiled)
+    LaunchFn launch_quarter, launch_quarter_inverse;
     const void* func;
 };
 
-// All configurations for one dtype, in order of preference per (mode, log_nu).
-const KernelCfg* kernel_table_f16(int* count);
-const KernelCfg* kernel_table_f32(int* count);
-const KernelCfg* kernel_table_f16f32(int* count);
+// The compiled parts of a dtype's configurations: each part's table has every
+// configuration, with mode -1 where another part compiles it (or none does).
+constexpr int kParts = 3;
+constexpr int kernel_part(int mode, int log_nu) { return mode != 0 ? 2 : (log_nu > 11 ? 1 : 0); }
+template <int PART> const KernelCfg* kernel_table_f16(int* count);
+template <int PART> const KernelCfg* kernel_table_f32(int* count);
+template <int PART> const KernelCfg* kernel_table_f16f32(int* count);
+template <> const KernelCfg* kernel_table_f16<0>(int* count);
+template <> const KernelCfg* kernel_table_f16<1>(int* count);
+template <> const KernelCfg* kernel_table_f16<2>(int* count);
+template <> const KernelCfg* kernel_table_f32<0>(int* count);
+template <> const KernelCfg* kernel_table_f32<1>(int* count);
+template <> const KernelCfg* kernel_table_f32<2>(int* count);
+template <> const KernelCfg* kernel_table_f16f32<0>(int* count);
+template <> const KernelCfg* kernel_table_f16f32<1>(int* count);
+template <> const KernelCfg* kernel_table_f16f32<2>(int* count);
 
 }  // namespace dsfft

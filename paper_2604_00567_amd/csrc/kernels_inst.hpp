@@ -1,7 +1,9 @@
 // Instantiates every configuration of configs.inc for one element type
 // (included by kernels_f16.hip / kernels_f32.hip / kernels_f16f32.hip with
 // ELEM_T (compute type), STORE_T (storage type of the plan's input and
-// output, ELEM_T if not defined), DTYPE_ID and TABLE_FN).
+// output, ELEM_T if not defined), DTYPE_ID and TABLE_FN).  Each file is
+// compiled kParts times, KERNEL_PART = 0 .. kParts - 1, with a share of the
+// configurations each, so that the parts compile side by side.
 #include <type_traits>
 
 #include "fft_device.hpp"
@@ -30,6 +32,7 @@ struct IoOf {
 template <class E, class S, int LOG_NU, int LOG_E, int UPW, int MODE, int LR0, int LR1, int LR2, int STG,
           int LANE, int PIPE, int ENC>
 static constexpr bool cfg_fits() {
+    if (kernel_part(MODE, LOG_NU) != KERNEL_PART) return false;
     if constexpr (!std::is_same_v<E, S>)
         if ((STG && LANE) || PIPE == 1) return false;
     // the radix-4 form: whole transforms stored as computed, no lane tail, no
@@ -38,6 +41,9 @@ static constexpr bool cfg_fits() {
         if (!std::is_same_v<E, S> || MODE != MODE_SMALL || LANE || PIPE == 1 || PIPE == 2 || PIPE == 5)
             return false;
         if (LR0 % 2 != LOG_NU % 2 || LR1 % 2 || LR2 % 2) return false;
+    } else if (is_quarter(ENC)) {
+        // a form of the plain kernels with ENC_TABLE
+        if (PIPE == 1 || LANE) return false;
     } else if (ENC != ENC_TABLE &&
                (!std::is_same_v<E, uint32_t> || !std::is_same_v<E, S> || PIPE == 1 || LANE)) {
         // the path-encoding variants: binary16 plans, plain (non-pipelined, no lane tail) kernels
@@ -109,6 +115,31 @@ static hipError_t launch_unit(const void* in, void* out, const void* lt, int64_t
     }
 }
 
+// Whether quarter.inc lists a configuration.
+static constexpr bool quarter_listed(int mode, int log_nu, int log_e, int upw, int upl, int lr0, int lr1, int lr2,
+                                     int stg, int pipe) {
+#define QUARTER(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, PIPE, UPL)                                      \
+    if (mode == MODE && log_nu == LOG_NU && log_e == LOG_E && upw == UPW && upl == UPL && lr0 == LR0 &&       \
+        lr1 == LR1 && lr2 == LR2 && stg == STG && pipe == PIPE)                                               \
+        return true;
+#include "quarter.inc"
+#undef QUARTER
+    return false;
+}
+
+// The launch of a configuration's form with encoding QENC (ENC_QUARTER or
+// ENC_QUARTER_INV); null where it has none.
+template <class E, class S, int LOG_NU, int LOG_E, int UPW, int UPL, int MODE, int LR0, int LR1, int LR2,
+          int STG, int LANE, int PIPE, int ENC, int QENC>
+static constexpr LaunchFn launch_quarter() {
+    if constexpr (ENC == ENC_TABLE && !LANE &&
+                  quarter_listed(MODE, LOG_NU, LOG_E, UPW, UPL, LR0, LR1, LR2, STG, PIPE) &&
+                  cfg_fits<E, S, LOG_NU, LOG_E, UPW, MODE, LR0, LR1, LR2, STG, LANE, PIPE, QENC>())
+        return &launch_unit<E, S, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, QENC>;
+    else
+        return nullptr;
+}
+
 // An entry that is not compiled gets mode -1: no plan or tuner ever selects it.
 #define CFGE(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL, ENC)              \
     {DTYPE_ID,                                                                                 \
@@ -120,6 +151,10 @@ static hipError_t launch_unit(const void* in, void* out, const void* lt, int64_t
      unit_lds_bytes<ELEM_T, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE,                               \
                     PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC>(),                             \
      &launch_unit<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC>, \
+     launch_quarter<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC, \
+                    ENC_QUARTER>(),                                                                   \
+     launch_quarter<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC, \
+                    ENC_QUARTER_INV>(),                                                               \
      kernel_entry<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC>()},
 #define CFGU(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL)                   \
     CFGE(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL, ENC_TABLE)
@@ -133,7 +168,8 @@ static const KernelCfg kTable[] = {
 #undef CFGU
 #undef CFGE
 
-const KernelCfg* TABLE_FN(int* count) {
+template <>
+const KernelCfg* TABLE_FN<KERNEL_PART>(int* count) {
     *count = (int)(sizeof(kTable) / sizeof(kTable[0]));
     return kTable;
 }

@@ -14,6 +14,7 @@ struct DeviceTable {
     void* ptr = nullptr;
     int64_t ncap = 0;
     size_t bytes = 0;
+    bool quarter = false;    // holds the quarter symmetry (quarter_symmetric)
     ~DeviceTable();
 };
 

@@ -114,6 +114,32 @@ std::vector<uint8_t> build_level_table(int64_t ncap, int dtype, int kind, bool i
     return img;
 }
 
+bool quarter_symmetric(const std::vector<uint8_t>& img, int64_t ncap, int dtype, bool inverse) {
+    // sign, multiplier and ratio as bit patterns in the table's precision
+    struct Bits {
+        uint32_t sm, m, t;
+        bool sine;
+    };
+    const uint32_t neg = dtype == DT_F16 ? 0x8000u : 0x80000000u;
+    const size_t eb = entry_bytes(dtype);
+    auto entry = [&](int64_t i) {
+        uint32_t u[4];
+        std::memcpy(u, img.data() + (size_t)i * eb, eb);
+        if (dtype == DT_F16) return Bits{u[0] & 0xffffu, u[0] >> 16, u[1] >> 16, (u[1] & 16u) != 0};
+        return Bits{u[0], u[1], u[2], u[3] != 0};
+    };
+    if (ncap < 4) return false;
+    const uint32_t t0 = entry(2).t, t1 = entry(3).t;
+    for (int64_t L = 4; L <= ncap; L <<= 1)
+        for (int64_t j = 0; j < L / 4; ++j) {
+            const Bits a = entry(L / 2 + j), b = entry(L / 2 + L / 4 + j);
+            const uint32_t sm = inverse ? a.m ^ neg : a.m, m = inverse ? a.sm : a.sm ^ neg;
+            if (b.sine == a.sine || b.sm != sm || b.m != m) return false;
+            if (j == 0 ? (a.t != t0 || b.t != t1) : b.t != (a.t ^ neg)) return false;
+        }
+    return true;
+}
+
 Radix4Entry radix4_entry(int64_t j, int64_t L, int kind, bool inverse) {
     Radix4Entry e;
     for (int p = 0; p < 3; ++p) e.w[p] = twiddle64((p + 1) * j, L, kind, inverse);

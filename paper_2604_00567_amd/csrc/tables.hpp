@@ -30,6 +30,12 @@ size_t entry_bytes(int dtype);
 // that many leading entries whatever sizes their plan or batch holds.
 constexpr int64_t kMinTableEntries = 4096;
 std::vector<uint8_t> build_level_table(int64_t ncap, int dtype, int kind, bool inverse);
+// Whether a device image holds the quarter symmetry that kernels with
+// ENC_QUARTER rely on, bit for bit at every level L >= 4: entry j + L/4
+// (j < L/4) is on the other path with multipliers (sigma' m', m') =
+// (m, -sigma m) (inverse: (-m, sigma m)) and, for j > 0, ratio -t; the ratios
+// of j = 0 and j = L/4 are the same two values at every level.
+bool quarter_symmetric(const std::vector<uint8_t>& img, int64_t ncap, int dtype, bool inverse);
 
 // Radix-4 form (Sec. VI, generality): the butterfly of span L and column j
 // uses the entries of W_L^j, W_L^2j and W_L^3j (3j may reach 3L/4) and the
