@@ -64,13 +64,15 @@ struct BatchGeo {
     static constexpr int kEncoding = ENC_TABLE;
     // an item's units need not be consecutive in memory
     static constexpr bool kBlockRsrc = false;
+    // a column or row item's units lie in one transform
+    static constexpr bool kTransformRsrc = true;
     const int64_t* offs;
     BatchItem it;
     int lane_id;       // threadIdx.x, made opaque per configuration (batch_unit)
     template <int LOG_NU, int MODE>
     __device__ __forceinline__ UnitGeom get(int ul) const {
         UnitGeom u;
-        u.in_stride = u.out_stride = 1;
+        u.out_stride = 1;
         u.q0 = 0;
         u.log_lb = 0;
         if (MODE == MODE_SMALL) {
@@ -80,7 +82,7 @@ struct BatchGeo {
             const int r0 = it.first + ul;
             u.base_in = it.in_off + r0;
             u.base_out = it.out_off + r0;
-            u.in_stride = u.out_stride = int64_t(1) << it.log_m;
+            u.out_stride = int64_t(1) << it.log_m;
         } else {
             const int q0 = it.first + ul;
             u.q0 = q0;
@@ -95,6 +97,10 @@ struct BatchGeo {
     __device__ __forceinline__ int tid() const { return lane_id; }
     __device__ __forceinline__ int64_t block_first(int) const { return 0; }
     __device__ __forceinline__ int64_t block_units(int) const { return 0; }
+    __device__ __forceinline__ int64_t transform_in(int) const { return it.in_off; }
+    __device__ __forceinline__ int64_t transform_out(int) const { return it.out_off; }
+    __device__ __forceinline__ int first_unit() const { return it.first; }
+    __device__ __forceinline__ int log_units() const { return it.log_m; }
 };
 
 template <class E, int LOG_NU, int LOG_E, int UPW, int MODE, int LR0, int LR1, int LR2, class Geo>
@@ -178,13 +184,14 @@ struct ListGeo {
     static constexpr int kEncoding = ENC_TABLE;
     // one unit per workgroup (the transform at offs[ublk])
     static constexpr bool kBlockRsrc = true;
+    static constexpr bool kTransformRsrc = false;
     const int64_t* offs;
     int64_t ublk, units;
     int lane_id;
     template <int LOG_NU, int MODE>
     __device__ __forceinline__ UnitGeom get(int ul) const {
         UnitGeom u;
-        u.in_stride = u.out_stride = 1;
+        u.out_stride = 1;
         u.q0 = 0;
         u.log_lb = 0;
         u.base_in = u.base_out = (ublk + ul < units) ? offs[ublk + ul] : 0;

@@ -474,6 +474,35 @@ __device__ __forceinline__ rsrc_t block_rsrc(const S* base, int64_t elems) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<S*>(base), 0, (int)(elems * (int64_t)sizeof(S)),
                                              0x00020000);
 }
+// Strided accesses of column and row units: the element stride is the same for
+// the whole wave but not known when compiled, so through global instructions
+// each access costs two or more 64-bit vector operations for its address (a third
+// of the vector instructions of the binary16 2^9-point column kernel).  Through a
+// buffer resource over the transform the multiples of the stride sit in the
+// instruction's scalar offset.  128 MiB of binary16 columns of 2^9 points
+// (2^17): 49.2 -> 46.1 us, of 2^10 (2^20, 16 per workgroup): 53 -> 50 us;
+// binary32 columns of 2^8: 46 -> 43 us.  Lanes that move more than 128 bytes keep the
+// global form: with these the compiler holds fewer loads and twiddles at a
+// time (binary32 2^10-point columns: 96 registers instead of 149 and 62
+// against 58 us).  S: the type that is stored.
+template <class S, int LOG_E>
+constexpr bool scalar_strides() {
+    return (sizeof(S) << LOG_E) <= 128;
+}
+// The resource over one transform of `bytes` at `base`, both the same for the
+// whole wave.  They go through readfirstlane behind an empty asm statement: the
+// compiler may compute a uniform value in vector registers, and a descriptor
+// there would be read lane by lane in a loop around each access.
+__device__ __forceinline__ uint32_t scalar32(uint32_t x) {
+    asm("" : "+v"(x));
+    return __builtin_amdgcn_readfirstlane(x);
+}
+template <class S>
+__device__ __forceinline__ rsrc_t transform_rsrc(const S* base, uint32_t bytes) {
+    const uint64_t p = (uint64_t)(uintptr_t)base;
+    const uint64_t q = ((uint64_t)scalar32((uint32_t)(p >> 32)) << 32) | scalar32((uint32_t)p);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)q, 0, (int)scalar32(bytes), 0x00020000);
+}
 // Cache policy: 2 = non-temporal (streaming), as __builtin_nontemporal_load/store.
 // A constant offset below 4096 fits the instruction's own offset field; larger
 // ones go to the scalar offset register.
@@ -488,6 +517,28 @@ __device__ __forceinline__ E buf_load(rsrc_t r, uint32_t lane_off, uint32_t c) {
         static_assert(sizeof(S) == 8, "binary16 or binary32 pairs");
         const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, STREAM ? 2 : 0);
         return to_compute(__builtin_bit_cast(S, u), E{});
+    }
+}
+// The same at a wave-uniform offset c that is not known when compiled.
+template <bool STREAM, class E, class S>
+__device__ __forceinline__ E buf_load_at(rsrc_t r, uint32_t lane_off, uint32_t c) {
+    if constexpr (sizeof(S) == 4) {
+        const uint32_t u = __builtin_amdgcn_raw_buffer_load_b32(r, lane_off, c, STREAM ? 2 : 0);
+        return to_compute(__builtin_bit_cast(S, u), E{});
+    } else {
+        static_assert(sizeof(S) == 8, "binary16 or binary32 pairs");
+        const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, c, STREAM ? 2 : 0);
+        return to_compute(__builtin_bit_cast(S, u), E{});
+    }
+}
+template <bool STREAM, class E, class S>
+__device__ __forceinline__ void buf_store_at(E v, rsrc_t r, uint32_t lane_off, uint32_t c) {
+    const S s = to_storage(v, S{});
+    if constexpr (sizeof(S) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, s), r, lane_off, c, STREAM ? 2 : 0);
+    } else {
+        typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, s), r, lane_off, c, STREAM ? 2 : 0);
     }
 }
 template <bool STREAM, class E, class S>
@@ -733,14 +784,14 @@ constexpr bool unit_fits() {
 
 // Geometry of one unit inside its transform.
 struct UnitGeom {
-    int64_t base_in, base_out, in_stride, out_stride;
+    int64_t base_in, base_out, out_stride;
     int q0, log_lb;
 };
 
 template <int LOG_NU, int MODE>
 __device__ __forceinline__ UnitGeom unit_geom(int64_t unit, int log_m) {
     UnitGeom u;
-    u.in_stride = u.out_stride = 1;
+    u.out_stride = 1;
     u.q0 = 0;
     u.log_lb = 0;
     if (MODE == MODE_SMALL) {
@@ -749,7 +800,7 @@ __device__ __forceinline__ UnitGeom unit_geom(int64_t unit, int log_m) {
         const int64_t b = unit >> log_m;
         const int64_t r0 = unit & ((int64_t(1) << log_m) - 1);
         u.base_in = u.base_out = (b << (log_m + LOG_NU)) + r0;
-        u.in_stride = u.out_stride = int64_t(1) << log_m;
+        u.out_stride = int64_t(1) << log_m;
     } else {
         const int64_t b = unit >> log_m;
         u.q0 = (int)(unit & ((int64_t(1) << log_m) - 1));
@@ -883,6 +934,10 @@ struct GridGeoT {
     static constexpr int kEncoding = ENC;
     // a workgroup's units are consecutive in memory (block_first, block_units)
     static constexpr bool kBlockRsrc = true;
+    // column and row units of one workgroup lie in one transform
+    // (transform_in, transform_out, first_unit, log_units): a transform has
+    // at least 2^6 of either, a multiple of every UPW
+    static constexpr bool kTransformRsrc = true;
     int64_t ublk, units;
     int log_m;
     int lane_id;       // threadIdx.x (opaque per block in the persistent loop)
@@ -892,6 +947,10 @@ struct GridGeoT {
     }
     __device__ __forceinline__ bool active(int ul) const { return ublk + ul < units; }
     __device__ __forceinline__ int tid() const { return lane_id; }
+    __device__ __forceinline__ int64_t transform_in(int log_nu) const { return (ublk >> log_m) << (log_m + log_nu); }
+    __device__ __forceinline__ int64_t transform_out(int log_nu) const { return transform_in(log_nu); }
+    __device__ __forceinline__ int first_unit() const { return (int)ublk & ((1 << log_m) - 1); }
+    __device__ __forceinline__ int log_units() const { return log_m; }
     // staging: the workgroup's units are elements [first, first + count)
     __device__ __forceinline__ int64_t block_first(int log_nu) const { return ublk << log_nu; }
     __device__ __forceinline__ int64_t block_units(int upw) const {
@@ -927,6 +986,21 @@ __device__ __forceinline__ void load_pass0(E* v, const SI* in, const Geo& gp) {
     const int tid = gp.tid();
     const int ul0 = unit_fast ? (tid % UPW) : (tid / G) * UPL;
     const int g = unit_fast ? (tid / UPW) : (tid % G);
+    if constexpr (MODE == MODE_COLS && Geo::kTransformRsrc && scalar_strides<SI, LOG_E>()) {
+        // element r + M i of column c sits at (r + M i) 2^log_m + c of the
+        // transform: an offset of the lane and a scalar one
+        const int lm = gp.log_units();
+        const rsrc_t rs = transform_rsrc(in + gp.transform_in(LOG_NU), (uint32_t)sizeof(SI) << (LOG_NU + lm));
+#pragma unroll
+        for (int u = 0; u < GPL; ++u) {
+            const uint32_t lane_off = (uint32_t)((((g + G * u) << lm) + gp.first_unit() + ul0) * (int)sizeof(SI));
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                v[u * R + i] =
+                    buf_load_at<false, E, SI>(rs, lane_off, (uint32_t)((M * i) << lm) * (uint32_t)sizeof(SI));
+        }
+        return;
+    }
     if constexpr (MODE == MODE_SMALL && Geo::kBlockRsrc && NU * sizeof(SI) > 4096) {
         const rsrc_t rs = block_rsrc(in + gp.block_first(LOG_NU), gp.block_units(UPW) << LOG_NU);
 #pragma unroll
@@ -958,7 +1032,8 @@ __device__ __forceinline__ void load_pass0(E* v, const SI* in, const Geo& gp) {
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
                     const int64_t idx = r + (int64_t)M * i;
-                    vk[u * R + i] = load_elem<MODE != MODE_COLS && G * (int)sizeof(SI) >= 128, E>(in + geo.base_in + idx * geo.in_stride);
+                    vk[u * R + i] = load_elem<MODE != MODE_COLS && G * (int)sizeof(SI) >= 128, E>(
+                        in + geo.base_in + idx * (MODE == MODE_COLS ? geo.out_stride : 1));
                 }
             }
         } else {
@@ -1366,6 +1441,21 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                     }
                 }
             }
+        } else if constexpr (MODE != MODE_SMALL && Geo::kTransformRsrc && scalar_strides<SO, LOG_E>()) {
+            // output q + L0 e of the unit sits at (q + L0 e) 2^log_m + unit of
+            // the transform; streaming only where a wave's UPW consecutive rows
+            // fill whole lines (the column kernel's output is read back next)
+            const int lm = gp.log_units();
+            const rsrc_t rs = transform_rsrc(out + gp.transform_out(LOG_NU), (uint32_t)sizeof(SO) << (LOG_NU + lm));
+#pragma unroll
+            for (int u = 0; u < GPL; ++u) {
+                const uint32_t lane_off =
+                    (uint32_t)((((g + G * u) << lm) + gp.first_unit() + ul0) * (int)sizeof(SO));
+#pragma unroll
+                for (int e = 0; e < R; ++e)
+                    buf_store_at<MODE == MODE_ROWS && UPW * (int)sizeof(SO) >= 128, E, SO>(
+                        v[u * R + e], rs, lane_off, (uint32_t)((L0 * e) << lm) * (uint32_t)sizeof(SO));
+            }
         } else {
 #pragma unroll
             for (int k = 0; k < UPL; ++k) {
@@ -1381,8 +1471,8 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                             // G consecutive ones of a whole transform (as load_pass0), or the
                             // row kernel's UPW consecutive rows
                             store_elem<(MODE == MODE_SMALL && G * (int)sizeof(SO) >= 128) ||
-                                       (MODE == MODE_ROWS && UPW * (int)sizeof(SO) >= 128)>(v[k * EL + u * R + e],
-                                                           out + geo.base_out + idx * geo.out_stride);
+                                       (MODE == MODE_ROWS && UPW * (int)sizeof(SO) >= 128)>(
+                                v[k * EL + u * R + e], out + geo.base_out + idx * geo.out_stride);
                         }
                     }
                 }
@@ -1401,6 +1491,19 @@ template <class E, int LOG_NU, int LOG_E, int UPW, int UPL, int MODE, int LR0, i
           int LANE, int PIPE, class SI, class SO, int ENC>
 __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const TwT<E, ENC>* __restrict__ lt,
                                                  int64_t units, int log_m);
+
+// Order of the column kernel's blocks.  Consecutive workgroups go to the 8 XCDs
+// in turn, each with an L2 of its own, while consecutive blocks of UPW columns
+// read (and write) neighbouring 64-256 byte runs of the same rows.  Here each
+// XCD takes runs of kColumnRun consecutive blocks, so that the runs that
+// share a line or a DRAM page are in one L2 at one time.  Runs of 8 to 64 measure
+// alike; any remainder past whole groups of 8 runs keeps its order.
+constexpr int kColumnRun = 32;
+__device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk) {
+    constexpr int64_t group = 8 * kColumnRun;
+    if (b >= nblk / group * group) return b;
+    return b / group * group + b % 8 * kColumnRun + b % group / 8;
+}
 
 // SI, SO: storage types of the input and output (E unless the plan stores
 // binary16 and computes in binary32).
@@ -1514,8 +1617,8 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
         // PIPE = 5: the middle pass from LDS (as PIPE = 3) and the last pass's
         // twiddles prefetched a pass ahead (as PIPE = 2)
         constexpr int TWL = (PIPE == 3 || PIPE == 4 || PIPE == 5) ? PIPE : 0;
-        const GridGeoT<PIPE == 2 || PIPE == 5, ENC, TWL> gp{(int64_t)blockIdx.x * UPW, units, log_m,
-                                                             (int)threadIdx.x};
+        const int64_t blk = MODE == MODE_COLS ? column_block(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+        const GridGeoT<PIPE == 2 || PIPE == 5, ENC, TWL> gp{blk * UPW, units, log_m, (int)threadIdx.x};
         unit_pass<E, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, 0, 0>(v, lds, lt, in, out,
                                                                                gp);
     }
