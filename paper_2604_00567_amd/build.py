@@ -20,7 +20,7 @@ OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdsfft.so")
 
 HIP_SOURCES = ["api.cpp", "batch.cpp", "serve.cpp", "serve_loop.cpp", "tune.cpp", "scratch.cpp", "kernels_f16.hip", "kernels_f32.hip",
-               "kernels_f16f32.hip", "kernels_batch.hip"]
+               "kernels_f16f32.hip", "kernels_few.hip", "kernels_batch.hip"]
 CXX_SOURCES = ["tables.cpp"]
 # The kernel files hold every configuration of a precision; they are compiled
 # in parts (kParts in kernels.hpp), which run side by side.

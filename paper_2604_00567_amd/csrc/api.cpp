@@ -134,7 +134,8 @@ const KernelCfg* find_plain_kernel(int dtype, int mode, int log_nu, bool radix4 
 // The launch of configuration k for a plan: the form that takes the second
 // quarter of each stage's twiddles from the first wherever the plan's table
 // holds that symmetry (dual-select tables) and the form is compiled.
-static LaunchFn plan_launch(const fft_plan* p, const KernelCfg* k) {
+template <class Cfg>
+static LaunchFn plan_launch(const fft_plan* p, const Cfg* k) {
     const LaunchFn q = p->inverse ? k->launch_quarter_inverse : k->launch_quarter;
     return p->table->quarter && q ? q : k->launch;
 }
@@ -171,26 +172,100 @@ static int small_limit(int dtype) {
     return m;
 }
 
-// Small batches: the default and tuned configurations hold several
-// transforms per workgroup (tuned on 256 MiB batches).  When a launch would
-// have fewer workgroups than the device has compute units, its time is one
-// workgroup's walk through its transforms; the first plain configuration with
-// one transform per workgroup, where the size has one, finishes sooner
-// (binary32 N = 1024 x 16: 4.4 against 5.6 us per kernel; binary16 3.3 us).
-static void small_batch_choice(fft_plan* p) {
-    if (p->k2 || !p->k1 || p->k1->upw == 1) return;
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess) return;
-    if ((p->batch + p->k1->upw - 1) / p->k1->upw >= cus) return;
+// Calls of few transforms.  The default and tuned configurations are the
+// fastest for 256 MiB batches; where a launch has fewer workgroups than the
+// device has compute units, its time is one workgroup's walk through its
+// transforms, and shapes with more and shorter workgroups finish sooner.
+
+// The narrowest configuration of (dtype, mode, log_nu), fewest units per
+// workgroup, whose launch over `units` still has at most one workgroup per
+// compute unit; `tuned` if none has.  (More workgroups than that queue behind each
+// other, and the wider shapes use the memory lines better: binary16 2^18 x 1
+// 12.0 -> 7.5 us, x 8 15.8 -> 14.1; binary32 2^18 x 4 18.0 -> 13.1 us.)  A row kernel
+// may also be wider than the tuned one where that brings the launch down to
+// one round and two workgroups still share a compute unit (binary16 2^17 x 32 19.3
+// -> 17.2 us; with one per compute unit, binary16 2^18 x 32, 25.0 -> 27.3).
+static const KernelCfg* narrow_kernel(const KernelCfg* tuned, int64_t units, int cus) {
+    const KernelCfg* best = nullptr;
+    for (int v = 0;; ++v) {
+        const KernelCfg* k = find_kernel(tuned->dtype, tuned->mode, tuned->log_nu, v);
+        if (!k) return best ? best : tuned;
+        if (k->staged || k->encoding || (units + k->upw - 1) / k->upw > cus) continue;
+        if (k->upw > tuned->upw && (k->mode == MODE_COLS || 2 * k->lds_bytes > 160 * 1024)) continue;
+        // eight binary16 units of 2^10 points: 32-byte runs of 4 KiB strides, slower than sixteen
+        if (k->log_nu >= 10 && k->upw * work_elem_bytes(k->dtype) < 64) continue;
+        if (!best || k->upw < best->upw || (k->upw == best->upw && k->launch_quarter && !best->launch_quarter)) best = k;
+    }
+}
+
+// Whole transforms: the configuration with one transform per workgroup on
+// the most lanes (binary32 N = 1024 x 16: 4.4 against 5.6 us per kernel; 2^14 x
+// 256 18.5 against 21.1 us; binary16 2^15 x 96 13.1 against 16.2 us).
+static const KernelCfg* widest_kernel(const fft_plan* p) {
+    const KernelCfg* best = p->k1->upw == 1 ? p->k1 : nullptr;
     for (int v = 0;; ++v) {
         const KernelCfg* k = find_kernel(p->dtype, MODE_SMALL, p->log_n, v);
-        if (!k) return;
-        if (k->upw == 1 && !k->staged && !k->lane_tail && !k->pipelined && !k->encoding) {
-            p->k1 = k;
-            p->k1_plain = k;
-            return;
+        if (!k) return best ? best : p->k1;
+        if (k->upw != 1 || k->staged || k->lane_tail || k->encoding || k->pipelined == 1 || k->pipelined == 2) continue;
+        if (!best || k->threads > best->threads ||
+            (k->threads == best->threads && best != p->k1 && k->launch_quarter && !best->launch_quarter))
+            best = k;
+    }
+}
+
+// Up to how many transforms the split through the output beats the whole
+// transform, in sixteenths of the compute units; 0: never.  By bytes of a
+// transform: 64 KiB (binary16 2^14, binary32 2^13), 128 KiB, 256 KiB.  Below them
+// the whole transform takes less than two launches.  Split / whole in us at
+// and past the limits: binary16 2^14 x 48 7.6 / 7.8, x 64 8.5 / 7.9; 2^15 x 64
+// 11.8 / 12.8, x 96 15.6 / 13.1; 2^16 x 1 6.2 / 24.5, x 96 22.8 / 25.8, x 128
+// 28.3 / 27.2; binary32 2^13 x 48 8.3 / 8.5; 2^14 x 64 12.0 / 12.6; 2^15 x 96
+// 22.6 / 25.9.
+static int split_limit(int dtype, int log_n) {
+    if (dtype == DT_F16F32) return 0;      // its intermediate does not fit in its output
+    const int log_bytes = log_n + (dtype == DT_F16 ? 2 : 3);
+    switch (log_bytes) {
+        case 16: return 3;
+        case 17: return 4;
+        case 18: return 6;
+        default: return 0;
+    }
+}
+
+static const FewCfg* few_half(int dtype, int mode, int log_nu, int64_t units, int cus) {
+    int cnt = 0;
+    const FewCfg* t = few_table(&cnt);
+    const FewCfg* best = nullptr;
+    for (int i = 0; i < cnt; ++i) {
+        if (t[i].dtype != dtype || t[i].mode != mode || t[i].log_nu != log_nu) continue;
+        best = &t[i];
+        if (units / t[i].upw <= cus) break;
+    }
+    return best;
+}
+
+static void few_transforms_choice(fft_plan* p) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess) return;
+    if (p->k2) {
+        const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
+        p->k1 = p->k1_plain = narrow_kernel(p->k1, p->batch << m2, cus);
+        p->k2 = narrow_kernel(p->k2, p->batch << m1, cus);
+        return;
+    }
+    if (p->batch * 16 <= (int64_t)split_limit(p->dtype, p->log_n) * cus) {
+        const int m1 = (p->log_n + 1) / 2, m2 = p->log_n - m1;
+        const FewCfg* c = few_half(p->dtype, MODE_COLS, m1, p->batch << m2, cus);
+        const FewCfg* r = few_half(p->dtype, MODE_ROWS, m2, p->batch << m1, cus);
+        if (c && r) {
+            p->few_cols = c;
+            p->few_rows = r;
         }
     }
+    const int64_t wgs = (p->batch + p->k1->upw - 1) / p->k1->upw;
+    if (p->k1->upw == 1 ? wgs > cus : wgs >= cus) return;
+    const KernelCfg* k = widest_kernel(p);
+    if (k != p->k1) p->k1 = p->k1_plain = k;
 }
 
 int choose_schedule(fft_plan* p, const int* variants) {
@@ -247,6 +322,14 @@ void size_workspace(fft_plan* p) {
 int launch_plan_ws(const fft_plan* p, const void* in, void* out, hipStream_t s, void* ws, int64_t chunk) {
     const void* lt = p->table->ptr;
     if (!p->k2) {
+        if (p->few_cols && in != out) {
+            const int m1 = p->few_cols->log_nu, m2 = p->few_rows->log_nu;
+            hipError_t e = plan_launch(p, p->few_cols)(in, out, lt, p->batch << m2, m2, s);
+            if (e != hipSuccess) return hip_error(e, "launch(few, cols)");
+            e = plan_launch(p, p->few_rows)(out, out, lt, p->batch << m1, m1, s);
+            if (e != hipSuccess) return hip_error(e, "launch(few, rows)");
+            return FFT_OK;
+        }
         const bool aligned16 = (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
         const KernelCfg* k = (p->k1->staged && !aligned16) ? p->k1_plain : p->k1;
         hipError_t e = plan_launch(p, k)(in, out, lt, p->batch, 0, s);
@@ -315,7 +398,7 @@ fft_plan* plan_create(int64_t n, int64_t batch, int dtype, int kind, const int* 
     } else if (choose_schedule(p.get(), variants) != FFT_OK) {
         return nullptr;
     }
-    if (!variants && radix == 2) small_batch_choice(p.get());
+    if (!variants && radix == 2) few_transforms_choice(p.get());
     size_workspace(p.get());
     if (p->ws_need && alloc_ws) {
         e = hipMalloc(&p->ws, p->ws_need);
@@ -426,6 +509,9 @@ int fft_plan_info(const fft_plan* p, int64_t* n, int64_t* batch, int* dtype, int
     if (kind) *kind = p->kind;
     if (config_out && cap) {
         std::string d = describe(p->k1);
+        if (p->few_cols)
+            d += "; out of place: split through the output, " + std::to_string(p->few_cols->upw) + " columns and " +
+                 std::to_string(p->few_rows->upw) + " rows per workgroup";
         if (p->k2) d += " | " + describe(p->k2) + " | chunk=" + std::to_string(p->chunk);
         std::snprintf(config_out, cap, "%s", d.c_str());
     }

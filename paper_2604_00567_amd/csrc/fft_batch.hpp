@@ -66,6 +66,7 @@ struct BatchGeo {
     static constexpr bool kBlockRsrc = false;
     // a column or row item's units lie in one transform
     static constexpr bool kTransformRsrc = true;
+    static constexpr bool kThroughOutput = false;
     const int64_t* offs;
     BatchItem it;
     int lane_id;       // threadIdx.x, made opaque per configuration (batch_unit)
@@ -185,6 +186,7 @@ struct ListGeo {
     // one unit per workgroup (the transform at offs[ublk])
     static constexpr bool kBlockRsrc = true;
     static constexpr bool kTransformRsrc = false;
+    static constexpr bool kThroughOutput = false;
     const int64_t* offs;
     int64_t ublk, units;
     int lane_id;

@@ -921,8 +921,18 @@ __device__ __forceinline__ void lane_tail(E* v, const typename TwOf<E>::type* __
 // Where the units of one workgroup live: a regular launch takes UPW
 // consecutive units per workgroup (GridGeo); the uneven-batch kernel takes the
 // units of one work item (BatchGeo, in fft_batch.hpp).
-template <bool TWPF, int ENC = ENC_TABLE, int TWL = 0>
+// THROUGH_OUT: the two-pass schedule keeps its intermediate in the output
+// (kThroughOutput).
+template <bool TWPF, int ENC = ENC_TABLE, int TWL = 0, bool THROUGH_OUT = false>
 struct GridGeoT {
+    // Where the intermediate Y[r][q] (residue r, column q of the first half of
+    // the stages) sits in a transform.  false: at r + M q in a workspace, so that the
+    // column kernel writes where it read and a row unit reads consecutive
+    // elements.  true: at q + r N/M in the output itself, no workspace:
+    // these are the places that row unit q writes, so each row workgroup
+    // reads and overwrites its own elements only, and the column kernel
+    // writes each column's results to consecutive elements.
+    static constexpr bool kThroughOutput = THROUGH_OUT;
     // the next pass's twiddles are loaded a pass ahead (twiddle_prefetch)
     static constexpr bool kTwiddlePrefetch = TWPF;
     // passes read their twiddles from an LDS copy: 0 none, else the PIPE
@@ -966,6 +976,15 @@ using GridGeo = GridGeoT<false>;
 // consecutive lanes to consecutive units ("unit-fast", UPL = 1 only); every
 // other pass maps consecutive lanes to consecutive groups of one unit.
 
+// Whether pass p of a unit with np passes maps consecutive lanes to consecutive
+// units: wherever its global accesses are strided (columns of the input, the
+// row kernel's outputs, and its inputs where the intermediate lies in the output).
+template <class Geo, int MODE>
+constexpr bool unit_fast_pass(int p, int np) {
+    if (MODE == MODE_COLS) return !(Geo::kThroughOutput && p == np - 1);
+    return MODE == MODE_ROWS && (p == np - 1 || (Geo::kThroughOutput && p == 0));
+}
+
 // Pass-0 inputs of this lane straight from HBM (unstaged configurations):
 // group r = g + G u (residue r, span 1) takes elements r + M i, i < R.
 // The streaming hint is used only where a wave's accesses cover whole lines:
@@ -982,12 +1001,15 @@ __device__ __forceinline__ void load_pass0(E* v, const SI* in, const Geo& gp) {
     constexpr int R = 1 << PP::lr(0);
     constexpr int M = 1 << PP::log_m(0);
     constexpr int GPL = EL / R;
-    constexpr bool unit_fast = (MODE == MODE_COLS);
+    constexpr bool unit_fast = unit_fast_pass<Geo, MODE>(0, PP::NP);
+    constexpr bool strided = MODE != MODE_SMALL && unit_fast;
     const int tid = gp.tid();
     const int ul0 = unit_fast ? (tid % UPW) : (tid / G) * UPL;
     const int g = unit_fast ? (tid / UPW) : (tid % G);
-    if constexpr (MODE == MODE_COLS && Geo::kTransformRsrc && scalar_strides<SI, LOG_E>()) {
-        // element r + M i of column c sits at (r + M i) 2^log_m + c of the
+    static_assert(!Geo::kThroughOutput || (Geo::kTransformRsrc && scalar_strides<SI, LOG_E>()),
+                  "an intermediate in the output: lanes of at most 128 bytes");
+    if constexpr (strided && Geo::kTransformRsrc && scalar_strides<SI, LOG_E>()) {
+        // element r + M i of unit c sits at (r + M i) 2^log_m + c of the
         // transform: an offset of the lane and a scalar one
         const int lm = gp.log_units();
         const rsrc_t rs = transform_rsrc(in + gp.transform_in(LOG_NU), (uint32_t)sizeof(SI) << (LOG_NU + lm));
@@ -1155,7 +1177,7 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
         constexpr int M = 1 << LOGM;
         constexpr int GPL = EL / R;
         constexpr int NT_OF = (UPW / UPL) * G;
-        constexpr bool unit_fast = (MODE == MODE_COLS) || (MODE == MODE_ROWS && P == NP - 1);
+        constexpr bool unit_fast = unit_fast_pass<Geo, MODE>(P, NP);
         static_assert(UPL == 1 || (MODE == MODE_SMALL && !LANE && UPW % UPL == 0),
                       "several units per lane: whole-transform units without the lane tail");
         static_assert(!STG || !LANE || (sizeof(SI) == sizeof(E) && sizeof(SO) == sizeof(E)),
@@ -1441,6 +1463,19 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                     }
                 }
             }
+        } else if constexpr (MODE == MODE_COLS && Geo::kThroughOutput) {
+            // output q + L0 e of column c at c N/M + q + L0 e of the transform
+            static_assert(NP > 1, "row workgroups need a barrier between their loads and stores");
+            const int lm = gp.log_units();
+            const rsrc_t rs = transform_rsrc(out + gp.transform_out(LOG_NU), (uint32_t)sizeof(SO) << (LOG_NU + lm));
+#pragma unroll
+            for (int u = 0; u < GPL; ++u) {
+                const uint32_t lane_off =
+                    (uint32_t)((((gp.first_unit() + ul0) << LOG_NU) + g + G * u) * (int)sizeof(SO));
+#pragma unroll
+                for (int e = 0; e < R; ++e)
+                    buf_store<false, E, SO>(v[u * R + e], rs, lane_off, (uint32_t)(L0 * e * (int)sizeof(SO)));
+            }
         } else if constexpr (MODE != MODE_SMALL && Geo::kTransformRsrc && scalar_strides<SO, LOG_E>()) {
             // output q + L0 e of the unit sits at (q + L0 e) 2^log_m + unit of
             // the transform; streaming only where a wave's UPW consecutive rows
@@ -1622,6 +1657,21 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
         unit_pass<E, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, 0, 0>(v, lds, lt, in, out,
                                                                                gp);
     }
+}
+
+// Column or row kernel of a two-pass schedule whose intermediate lies in the
+// output (kThroughOutput): whole-transform sizes in calls of few transforms,
+// which would leave most compute units without a workgroup.
+template <class E, int LOG_NU, int LOG_E, int UPW, int MODE, int LR0, int LR1, int LR2, int ENC>
+__global__ void __launch_bounds__(UPW << (LOG_NU - LOG_E))
+fft_few_kernel(const E* in, E* out, const typename TwOf<E>::type* __restrict__ lt, int64_t units, int log_m) {
+    static_assert(MODE == MODE_COLS || MODE == MODE_ROWS, "one half of a two-pass schedule");
+    static_assert(LR0 + LR1 + LR2 == LOG_NU && LR1 > 0, "two or three passes");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    E* lds = reinterpret_cast<E*>(lds_raw);
+    E v[1 << LOG_E];
+    const GridGeoT<false, ENC, 0, true> gp{(int64_t)blockIdx.x * UPW, units, log_m, (int)threadIdx.x};
+    unit_pass<E, LOG_NU, LOG_E, UPW, 1, MODE, LR0, LR1, LR2, 0, 0, 0, 0>(v, lds, lt, in, out, gp);
 }
 
 }  // namespace dsfft

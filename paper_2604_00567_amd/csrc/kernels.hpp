@@ -33,6 +33,14 @@ struct KernelCfg {
     const void* func;
 };
 
+// One half of the two-pass schedule through the output (kernels_few.hip);
+// units: columns or rows of the launch, log_m: log2 of those in a transform.
+struct FewCfg {
+    int dtype, mode, log_nu, upw;
+    LaunchFn launch, launch_quarter, launch_quarter_inverse;
+};
+const FewCfg* few_table(int* count);
+
 // The compiled parts of a dtype's configurations: each part's table has every
 // configuration, with mode -1 where another part compiles it (or none does).
 constexpr int kParts = 3;

@@ -43,6 +43,10 @@ struct fft_plan {
     const dsfft::KernelCfg* k1 = nullptr;   // single kernel, or the column kernel
     const dsfft::KernelCfg* k1_plain = nullptr;  // k1's size without 16-byte staging
     const dsfft::KernelCfg* k2 = nullptr;   // row kernel of the two-pass schedule
+    // calls of few whole transforms that are not in place: the two halves of
+    // the schedule through the output (null: k1 serves every call)
+    const dsfft::FewCfg* few_cols = nullptr;
+    const dsfft::FewCfg* few_rows = nullptr;
     int64_t chunk = 0;                      // transforms per two-pass chunk
     size_t ws_need = 0, ws_bytes = 0;
     void* ws = nullptr;
