@@ -196,7 +196,7 @@ void build_work(const int64_t* n, const int64_t* off, int64_t count, const int* 
 }
 
 static int build_items(fft_batch* b) {
-    if (batch_resident_grid(b->dtype, b->device, &b->resident) != FFT_OK) return FFT_EHIP;
+    if (batch_resident_grid(b->dtype, b->table->quarter, b->device, &b->resident) != FFT_OK) return FFT_EHIP;
     int64_t ws_elems = 0;
     build_work(b->n.data(), b->offset.data(), b->count, b->cfg_choice, lists_for(b->dtype),
                b->items, b->offs, b->lists, b->nlist, ws_elems, b->phase0);
@@ -206,11 +206,11 @@ static int build_items(fft_batch* b) {
 
 // Resident workgroups of the persistent kernel (its grid when the work list is
 // long enough).
-int batch_resident_grid(int dtype, int device, int* out) {
+int batch_resident_grid(int dtype, bool quarter, int device, int* out) {
     int cus = 0, per_cu = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return hip_error(e, "hipDeviceGetAttribute");
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel_func(dtype),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel_func(dtype, quarter),
                                                      kHostBatchThreads, batch_lds_bytes(dtype));
     if (e != hipSuccess) return hip_error(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     *out = cus * std::max(per_cu, 1);
@@ -282,7 +282,7 @@ struct PhaseArgs {
 
 static hipKernelNodeParams phase_params(const fft_batch* b, PhaseArgs& a, int phase) {
     hipKernelNodeParams kp{};
-    kp.func = const_cast<void*>(batch_kernel_func(b->dtype));
+    kp.func = const_cast<void*>(batch_kernel_func(b->dtype, b->table->quarter));
     kp.gridDim = dim3(phase == 0 ? b->grid0 : b->grid1);
     kp.blockDim = dim3(kHostBatchThreads);
     kp.sharedMemBytes = (unsigned)batch_lds_bytes(b->dtype);
@@ -309,7 +309,7 @@ struct ListArgs {
 
 static hipKernelNodeParams list_params(const fft_batch* b, ListArgs& a, int list) {
     hipKernelNodeParams kp{};
-    kp.func = const_cast<void*>(batch_list_func(list));
+    kp.func = const_cast<void*>(batch_list_func(list, b->table->quarter));
     kp.gridDim = dim3((unsigned)b->nlist[list]);
     kp.blockDim = dim3(kListThreads);
     kp.sharedMemBytes = (unsigned)batch_list_lds_bytes(list);

@@ -62,25 +62,26 @@ void build_work(const int64_t* n, const int64_t* off, int64_t count, const int* 
 // list-kernel sizes take none, and each split transform takes its column and
 // row items.
 int64_t work_items_of_class(int dtype, int m, int64_t count);
-int batch_resident_grid(int dtype, int device, int* out);
+int batch_resident_grid(int dtype, bool quarter, int device, int* out);
 
 size_t batch_lds_bytes(int dtype);
-const void* batch_kernel_func(int dtype);
+// quarter: the form for a table with the quarter symmetry (DeviceTable::quarter).
+const void* batch_kernel_func(int dtype, bool quarter);
 size_t batch_list_lds_bytes(int list);
-const void* batch_list_func(int list);
-hipError_t launch_batch_list(int list, const void* in, void* out, const void* lt, const int64_t* offs,
-                             int64_t count, hipStream_t s);
+const void* batch_list_func(int list, bool quarter);
+hipError_t launch_batch_list(int list, bool quarter, const void* in, void* out, const void* lt,
+                             const int64_t* offs, int64_t count, hipStream_t s);
 
 // Queue words per batch or serving slot: (head, workgroups done) for each of
 // the two phases; zero when allocated, and left zero by every launch.
 constexpr int kQueueWords = 4;
 // One phase: items first .. first + nitems - 1, queue words q[0..1].
-hipError_t launch_batch(int dtype, const void* in, void* out, void* ws, const void* lt,
+hipError_t launch_batch(int dtype, bool quarter, const void* in, void* out, void* ws, const void* lt,
                         const void* items, const int64_t* offs, int first, int nitems,
                         unsigned* q, int grid, hipStream_t s);
 // Both phases of a work list (phase 0 on ctl[0..1], phase 1 on ctl[2..3]) on
 // stream s.
-hipError_t launch_batch_phases(int dtype, const void* in, void* out, void* ws, const void* lt,
+hipError_t launch_batch_phases(int dtype, bool quarter, const void* in, void* out, void* ws, const void* lt,
                                const void* items, const int64_t* offs, int phase0, int nitems,
                                unsigned* ctl, int grid0, int grid1, hipStream_t s);
 

@@ -53,15 +53,16 @@ constexpr size_t batch_prefix_bytes() {
 //   out_off    column items: transform start in the workspace; row items: in the output
 using BatchItem = HostBatchItem;
 
-// Unit geometry of one work item (TPX: the LDS table prefix).
-template <int TPX>
+// Unit geometry of one work item (TPX: the LDS table prefix; ENC: ENC_TABLE, or
+// ENC_QUARTER for a table with the quarter symmetry).
+template <int TPX, int ENC>
 struct BatchGeo {
     // no twiddle prefetch: the kernel's registers are the largest over all its
     // configurations, and prefetching raises that maximum into spills
     static constexpr bool kTwiddlePrefetch = false;
     static constexpr int kTwiddleLds = 0;
     static constexpr int kTwiddlePrefix = TPX;
-    static constexpr int kEncoding = ENC_TABLE;
+    static constexpr int kEncoding = ENC;
     // an item's units need not be consecutive in memory
     static constexpr bool kBlockRsrc = false;
     // a column or row item's units lie in one transform
@@ -177,12 +178,12 @@ __device__ __forceinline__ void batch_dispatch(int cfg, E* lds,
 // 2^16 points) run in a kernel of their own, one transform per workgroup,
 // with unit u of the launch at element offset offs[u]; table entries [0, TPX)
 // sit in LDS below the exchange area (the middle pass reads them there).
-template <int TPX>
+template <int TPX, int ENC>
 struct ListGeo {
     static constexpr bool kTwiddlePrefetch = false;
     static constexpr int kTwiddleLds = 0;
     static constexpr int kTwiddlePrefix = TPX;
-    static constexpr int kEncoding = ENC_TABLE;
+    static constexpr int kEncoding = ENC;
     // one unit per workgroup (the transform at offs[ublk])
     static constexpr bool kBlockRsrc = true;
     static constexpr bool kTransformRsrc = false;
@@ -205,7 +206,7 @@ struct ListGeo {
     __device__ __forceinline__ int64_t block_units(int) const { return ublk < units ? 1 : 0; }
 };
 
-template <class E, int LOG_NU, int LOG_E, int LR0, int LR1, int LR2, int TPX>
+template <class E, int LOG_NU, int LOG_E, int LR0, int LR1, int LR2, int TPX, int ENC>
 __global__ void __launch_bounds__(1 << (LOG_NU - LOG_E))
 fft_list_kernel(const E* in, E* out, const typename TwOf<E>::type* __restrict__ lt,
                 const int64_t* __restrict__ offs, int64_t count) {
@@ -216,7 +217,7 @@ fft_list_kernel(const E* in, E* out, const typename TwOf<E>::type* __restrict__ 
     copy_table_prefix<TW, TPX, (1 << (LOG_NU - LOG_E))>(lt, lds_raw);
     E* lds = reinterpret_cast<E*>(lds_raw + (size_t)TPX * sizeof(TW));
     E v[1 << LOG_E];
-    const ListGeo<TPX> gp{offs, (int64_t)blockIdx.x, count, (int)threadIdx.x};
+    const ListGeo<TPX, ENC> gp{offs, (int64_t)blockIdx.x, count, (int)threadIdx.x};
     unit_pass<E, LOG_NU, LOG_E, 1, 1, MODE_SMALL, LR0, LR1, LR2, 0, 0, 0, 0>(v, lds, lt, in, out, gp);
 }
 
@@ -224,7 +225,7 @@ fft_list_kernel(const E* in, E* out, const typename TwOf<E>::type* __restrict__ 
 // head and q[1] counts the workgroups that have left the loop; both are zero
 // at launch, and the last workgroup to leave sets them back to zero for the
 // next launch on the stream (so no clearing launch is needed).
-template <class E>
+template <class E, int ENC>
 __global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(sizeof(E) == 4 ? 4 : 2)))
 fft_batch_kernel(const E* in, E* out, E* ws, const typename TwOf<E>::type* __restrict__ lt,
                  const BatchItem* __restrict__ items, const int64_t* __restrict__ offs,
@@ -250,7 +251,7 @@ fft_batch_kernel(const E* in, E* out, E* ws, const typename TwOf<E>::type* __res
         // the returned index is needed only at the end of the item
         const unsigned next = threadIdx.x == 0 ? atomicAdd(head, 1u) : 0u;
         const BatchItem it = items[first + idx];
-        const BatchGeo<batch_twiddle_prefix<E>()> geo{offs, it, 0};
+        const BatchGeo<batch_twiddle_prefix<E>(), ENC> geo{offs, it, 0};
         // An opaque copy of the table pointer per item keeps each case's
         // twiddle address arithmetic inside the loop; hoisted out of it, the
         // addresses of every case would stay live across the whole loop.

@@ -85,7 +85,7 @@ fft_serve_slot* fft_serve_slot_create(fft_dtype dtype, fft_table_kind kind, int6
         hip_error(e, "hipMemset(queue words)");
         return nullptr;
     }
-    if (batch_resident_grid(s->dtype, s->device, &s->resident) != FFT_OK) return nullptr;
+    if (batch_resident_grid(s->dtype, s->table->quarter, s->device, &s->resident) != FFT_OK) return nullptr;
     if ((e = hipEventCreateWithFlags(&s->done, hipEventDisableTiming)) != hipSuccess) {
         hip_error(e, "hipEventCreate");
         return nullptr;
@@ -139,7 +139,7 @@ int fft_serve_slot_launch(fft_serve_slot* s, const int64_t* n, const int64_t* ba
         return hip_error(e, "hipMemcpyAsync(work list)");
     const int64_t* d_lists = (const int64_t*)(s->d_stage + ib + ob);
     for (int i = 0; i < kNumLists; ++i) {
-        if (s->nlist[i] && (e = launch_batch_list(i, data, data, s->table->ptr, d_lists, s->nlist[i], st)) !=
+        if (s->nlist[i] && (e = launch_batch_list(i, s->table->quarter, data, data, s->table->ptr, d_lists, s->nlist[i], st)) !=
                                hipSuccess)
             return hip_error(e, "launch(list)");
         d_lists += s->nlist[i];
@@ -147,7 +147,7 @@ int fft_serve_slot_launch(fft_serve_slot* s, const int64_t* n, const int64_t* ba
     const int64_t n1 = (int64_t)s->items.size() - phase0;
     const int grid0 = (int)std::max<int64_t>(1, std::min<int64_t>(phase0, s->resident));
     const int grid1 = (int)std::max<int64_t>(1, std::min<int64_t>(n1, s->resident));
-    if ((e = launch_batch_phases(s->dtype, data, data, s->ws, s->table->ptr, s->d_stage,
+    if ((e = launch_batch_phases(s->dtype, s->table->quarter, data, data, s->ws, s->table->ptr, s->d_stage,
                                  (const int64_t*)(s->d_stage + ib),
                                  (int)phase0, (int)s->items.size(), s->d_ctl, grid0, grid1, st)) !=
         hipSuccess)

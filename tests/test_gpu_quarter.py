@@ -63,3 +63,28 @@ def test_inverse(n, dtype):
 def test_other_tables(n, kind):
     x = inputs.uniform(n, 2, 43, "f32")
     assert mismatches(run_gpu(x, "f32", kind), oracle.emulate(x, kind, "f32")) == 0
+
+
+@pytest.mark.parametrize("dtype,kind", [("f16", "dual_select"), ("f32", "dual_select"), ("f32", "linzer_feig")])
+def test_uneven_batch_and_slot(dtype, kind):
+    """Every size class once, sparse inputs, through an uneven batch (out of
+    place) and a serving slot (in place)."""
+    import torch
+    sizes = [1 << m for m in range(1, 19)]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    x = np.concatenate([sparse(n, dtype, 90 + n % 83)[n.bit_length() % 3] if n > 2 else
+                        np.full((n, 2), 0.5, np.float32 if dtype == "f32" else np.float16) for n in sizes])
+    xt = torch.from_numpy(x).to("cuda:0")
+    yt = torch.full_like(xt, float("nan"))
+    batch = binding.Batch(sizes, dtype, kind)
+    batch.execute(xt, yt)
+    slot = binding.fft_serve_slot_create(dtype, kind, 1024, len(sizes), 8, 8 << 20)
+    binding.fft_serve_slot_launch(slot, sizes, [1] * len(sizes), off[:-1], xt.data_ptr(),
+                                  torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    binding.fft_serve_slot_destroy(slot)
+    batch.close()
+    for got in (yt.cpu().numpy(), xt.cpu().numpy()):
+        for n, a in zip(sizes, off):
+            ref = oracle.emulate(x[a:a + n][None], kind, dtype)
+            assert mismatches(got[a:a + n][None], ref) == 0, n
