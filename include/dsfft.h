@@ -279,12 +279,16 @@ int fft_config_count(int64_t n, fft_dtype dtype, int* single, int* cols, int* ro
  * orders each transform's row items after its column items.  Binary16
  * transforms of 2^16 and 2^15 points (256 and 128 KiB, more than the batch
  * kernel's LDS) run whole in two list kernels of their own, one transform per
- * 1024-thread workgroup, over lists of their offsets, concurrently with the
- * first (graph branches with no dependency: the transforms are disjoint).  The
- * launches form one HIP graph built at the first execute and replayed by
- * every execute (the kernels leave their work-queue counters at zero for the
- * next replay); new data pointers are set on the graph's kernel nodes.  The
- * batch owns a workspace of the summed sizes of its two-pass transforms.
+ * 1024-thread workgroup, over lists of their offsets.  In batches of more than
+ * 2^25 elements the launches form one HIP graph built at the first execute and
+ * replayed by every execute, whose list kernels run beside the first kernel
+ * (branches with no dependency: the transforms are disjoint); new data
+ * pointers are set on the graph's kernel nodes.  Smaller batches launch the
+ * kernels in order on the caller's stream, and the column and row halves of
+ * the transforms of a short list, with the intermediate in the output, unless
+ * the call is in place.  (The kernels leave their work-queue counters at zero
+ * for the next execute.)  The batch owns a workspace of the summed sizes of its
+ * two-pass transforms; it must not run concurrently on two streams.
  * Returns NULL on error.
  */
 fft_batch* fft_batch_create(const int64_t* n, int64_t count, fft_dtype dtype, fft_table_kind kind);

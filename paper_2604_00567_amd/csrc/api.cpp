@@ -221,7 +221,7 @@ static const KernelCfg* widest_kernel(const fft_plan* p) {
 // 11.8 / 12.8, x 96 15.6 / 13.1; 2^16 x 1 6.2 / 24.5, x 96 22.8 / 25.8, x 128
 // 28.3 / 27.2; binary32 2^13 x 48 8.3 / 8.5; 2^14 x 64 12.0 / 12.6; 2^15 x 96
 // 22.6 / 25.9.
-static int split_limit(int dtype, int log_n) {
+int split_limit(int dtype, int log_n) {
     if (dtype == DT_F16F32) return 0;      // its intermediate does not fit in its output
     const int log_bytes = log_n + (dtype == DT_F16 ? 2 : 3);
     switch (log_bytes) {
@@ -232,7 +232,7 @@ static int split_limit(int dtype, int log_n) {
     }
 }
 
-static const FewCfg* few_half(int dtype, int mode, int log_nu, int64_t units, int cus) {
+const FewCfg* few_half(int dtype, int mode, int log_nu, int64_t units, int cus) {
     int cnt = 0;
     const FewCfg* t = few_table(&cnt);
     const FewCfg* best = nullptr;

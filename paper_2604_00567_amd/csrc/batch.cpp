@@ -1,15 +1,18 @@
-// Uneven-size batch plans: work-item construction, the HIP graph of the two
-// persistent-kernel phases (fft_batch.hpp) and its replay.
+// Uneven-size batch plans: work-item construction, and the launches of the list
+// kernels and of the two persistent-kernel phases (fft_batch.hpp), in order or as
+// a HIP graph and its replay.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
 #include "batch_launch.hpp"
 #include "dsfft.h"
+#include "fft_device.hpp"
 #include "plan.hpp"
 #include "tables.hpp"
 
@@ -54,11 +57,12 @@ struct fft_batch {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     int64_t phase0 = 0;                    // items of phase 0 (the rest are phase 1)
-    int grid = 0, grid0 = 0, grid1 = 0, resident = 1;
+    int grid = 0, grid0 = 0, grid1 = 0, resident = 1, cus = 1;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraphNode_t knode[2] = {nullptr, nullptr};
     hipGraphNode_t lnode[dsfft::kNumLists] = {};   // list kernels (binary16 2^16, 2^15)
+    std::mutex launch_mu;
     const void* cap_in = nullptr;
     void* cap_out = nullptr;
     ~fft_batch();
@@ -371,6 +375,41 @@ static int retarget(fft_batch* b, const void* in, void* out) {
     return FFT_OK;
 }
 
+// Batches of up to kDirectElems elements launch their kernels one after the other
+// on the caller's stream; larger ones replay a graph whose list kernels and phase
+// 0 fill each other's tails.  A replay costs 20 us of launching with one node and
+// 50 us and more with three branches: binary16, 2^6 .. 2^16 points, 20
+// transforms 69 us by graph and 21 in order, 300 68 and 30, 2000 (25 M
+// elements) 77 and 65, 4096 (48 M) 118 and 127.  In order, a short list (as for
+// plans, split_limit) runs split through the output unless the call is in place.
+constexpr int64_t kDirectElems = int64_t(1) << 25;
+static int launch_direct(fft_batch* b, const void* in, void* out, hipStream_t s) {
+    // one call's launches stay together: the phases share the batch's workspace
+    std::lock_guard<std::mutex> lock(b->launch_mu);
+    hipError_t e = hipSuccess;
+    const void* lt = b->table->ptr;
+    const bool quarter = b->table->quarter;
+    const int64_t* offs = b->d_lists;
+    for (int i = 0; i < kNumLists; ++i) {
+        const int64_t count = b->nlist[i];
+        if (count == 0) continue;
+        const int log_n = kListLog[i], m1 = (log_n + 1) / 2, m2 = log_n - m1;
+        if (in != out && count * 16 <= (int64_t)split_limit(b->dtype, log_n) * b->cus) {
+            const FewCfg* c = few_half(b->dtype, MODE_COLS, m1, count << m2, b->cus);
+            const FewCfg* r = few_half(b->dtype, MODE_ROWS, m2, count << m1, b->cus);
+            e = (quarter ? c->list_quarter : c->list)(in, out, lt, count << m2, m2, offs, s);
+            if (e == hipSuccess) e = (quarter ? r->list_quarter : r->list)(out, out, lt, count << m1, m1, offs, s);
+        } else {
+            e = launch_batch_list(i, quarter, in, out, lt, offs, count, s);
+        }
+        if (e != hipSuccess) return hip_error(e, "launch(list)");
+        offs += count;
+    }
+    e = launch_batch_phases(b->dtype, quarter, in, out, b->ws, lt, b->d_items, b->d_offs, (int)b->phase0,
+                            (int)b->items.size(), b->d_ctl, b->grid0, b->grid1, s);
+    return e == hipSuccess ? FFT_OK : hip_error(e, "launch(batch)");
+}
+
 int batch_execute(fft_batch* b, const void* in, void* out, hipStream_t s) {
     if (!b) return set_error(FFT_EINVAL, "null batch");
     if (!in || !out) return set_error(FFT_EINVAL, "null data pointer");
@@ -383,6 +422,7 @@ int batch_execute(fft_batch* b, const void* in, void* out, hipStream_t s) {
         return set_error(FFT_EINVAL, "in and out partially overlap");
     if (b->items.empty() && b->lists.empty()) return FFT_OK;
     int rc = FFT_OK;
+    if (b->total <= kDirectElems) return launch_direct(b, in, out, s);
     if (!b->exec) rc = build_graph(b, in, out);
     else if (b->cap_in != in || b->cap_out != out) rc = retarget(b, in, out);
     if (rc != FFT_OK) return rc;
@@ -429,6 +469,11 @@ fft_batch* batch_create(const int64_t* n, int64_t count, int dtype, int kind, co
     hipError_t e = hipGetDevice(&b->device);
     if (e != hipSuccess) {
         hip_error(e, "hipGetDevice");
+        return nullptr;
+    }
+    e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device);
+    if (e != hipSuccess) {
+        hip_error(e, "hipDeviceGetAttribute");
         return nullptr;
     }
     if (get_table(nmax, dtype, kind, false, &b->table) != FFT_OK) return nullptr;

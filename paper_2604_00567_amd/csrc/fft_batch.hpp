@@ -232,24 +232,24 @@ fft_batch_kernel(const E* in, E* out, E* ws, const typename TwOf<E>::type* __res
                  int first, int nitems, unsigned* q) {
     unsigned* head = q;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    // the barrier after the first claim publishes the copy
+    // the barrier of the first item's first exchange publishes the copy (an item
+    // without an exchange reads nothing from it, and ends with a barrier)
     copy_table_prefix<typename TwOf<E>::type, batch_twiddle_prefix<E>(), kBatchThreads>(lt, lds_raw);
     E* lds = reinterpret_cast<E*>(lds_raw + batch_prefix_bytes<E>());
-    // Claims run one item ahead: the claim of the next item is issued when
-    // the current one starts, so its round trip overlaps the current item's
+    // A workgroup's first item is its own index (the grid is at most nitems), so
+    // that its data loads wait for no claim.  Claims run one item ahead: the
+    // claim of the next item is issued when the current one starts, so its round trip overlaps the current item's
     // work, and published in LDS when the item ends.  Two slots alternate:
     // the slot written at the end of item k was last read after the barrier
     // that ended item k - 2, and every thread has since passed the barrier
     // that ended item k - 1.
     __shared__ int s_item[2];
-    if (threadIdx.x == 0) s_item[0] = (int)atomicAdd(head, 1u);
-    __syncthreads();
     // the item index is uniform: in scalar registers, the item's fields and
     // the addresses derived from them stay scalar too
-    int idx = __builtin_amdgcn_readfirstlane(s_item[0]);
+    int idx = (int)blockIdx.x;
     for (int k = 1; idx < nitems; ++k) {
         // the returned index is needed only at the end of the item
-        const unsigned next = threadIdx.x == 0 ? atomicAdd(head, 1u) : 0u;
+        const unsigned next = threadIdx.x == 0 ? gridDim.x + atomicAdd(head, 1u) : 0u;
         const BatchItem it = items[first + idx];
         const BatchGeo<batch_twiddle_prefix<E>(), ENC> geo{offs, it, 0};
         // An opaque copy of the table pointer per item keeps each case's

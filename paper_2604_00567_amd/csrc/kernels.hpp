@@ -35,11 +35,21 @@ struct KernelCfg {
 
 // One half of the two-pass schedule through the output (kernels_few.hip);
 // units: columns or rows of the launch, log_m: log2 of those in a transform.
+typedef hipError_t (*FewListFn)(const void* in, void* out, const void* lt, int64_t units, int log_m,
+                                const int64_t* offs, hipStream_t stream);
 struct FewCfg {
     int dtype, mode, log_nu, upw;
     LaunchFn launch, launch_quarter, launch_quarter_inverse;
+    // over the transforms at a list of offsets (null where batches have none)
+    FewListFn list, list_quarter;
 };
 const FewCfg* few_table(int* count);
+// The one for a launch over `units`: the narrowest whose workgroups number at
+// most one per compute unit, else the widest; null if there is none.
+const FewCfg* few_half(int dtype, int mode, int log_nu, int64_t units, int cus);
+// Up to how many transforms the split beats the whole transform, in sixteenths
+// of the compute units.
+int split_limit(int dtype, int log_n);
 
 // The compiled parts of a dtype's configurations: each part's table has every
 // configuration, with mode -1 where another part compiles it (or none does).

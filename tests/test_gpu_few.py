@@ -93,3 +93,40 @@ def test_two_pass_plans_of_few_transforms(dtype, log_n, batch):
     print(f"few n=2^{log_n} {dtype} batch={batch} {config}", flush=True)
     for b in {0, batch - 1, batch // 2}:
         assert mismatches(y[b].cpu().numpy()[None], ref[b % len(x)][None]) == 0, b
+
+
+@pytest.mark.parametrize("short,long", [(3, 5), (49, 65), (97, 1)])
+def test_lists_of_small_batches(short, long):
+    """Binary16 batches below the graph's size: their 2^16 (`short`) and 2^15
+    (`long`) transforms on both sides of the split limits, mixed with others,
+    out of place, in place, and captured into a graph."""
+    import torch
+    rng = np.random.default_rng(short)
+    sizes = np.array([1 << 16] * short + [1 << 15] * long + [1 << 17, 4096, 64, 2], np.int64)
+    rng.shuffle(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    assert off[-1] <= 1 << 25
+    blocks = {int(n): inputs.uniform(int(n), 3, 7, "f16") for n in set(sizes.tolist())}
+    x = np.concatenate([blocks[int(n)][i % 3] for i, n in enumerate(sizes)])
+    ref = {n: oracle.emulate(b, "dual_select", "f16") for n, b in blocks.items()}
+    xt = torch.from_numpy(x).to("cuda:0")
+    yt = torch.full_like(xt, float("nan"))
+    batch = binding.Batch(sizes, "f16")
+    batch.execute(xt, yt)
+    zt = xt.clone()
+    batch.execute(zt, zt)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    wt = torch.empty_like(xt)
+    with torch.cuda.graph(graph):
+        batch.execute(xt, wt)
+    for _ in range(2):
+        wt.fill_(float("nan"))
+        batch.execute(xt, yt)
+        graph.replay()
+        torch.cuda.synchronize()
+    batch.close()
+    for got in (yt, zt, wt):
+        y = got.cpu().numpy()
+        for i, n in enumerate(sizes.tolist()):
+            assert mismatches(y[off[i]:off[i + 1]][None], ref[n][i % 3][None]) == 0, (i, n)
