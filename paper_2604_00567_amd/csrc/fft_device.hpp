@@ -743,18 +743,42 @@ constexpr int lds_twiddle_last_pass() {
     if (PP::log_m(1) >= 6 && G % 64 == 0) return 0;
     return 1;
 }
-template <int LOG_NU, int LOG_E, int MODE, int LANE, class PP, int PIPE>
+// With quarter symmetry the copy holds only the entries that are loaded, half of
+// them: of pass P those of c = 1 and of each later stage's first half, entry
+// q + L0 c at q + L0 quarter_slot(c) of the pass's part of the copy, which
+// follows the parts of the passes before it.  Binary32 2^13 then takes 38.9 KiB
+// of LDS instead of 42.5, four workgroups per CU instead of three: 256 MiB
+// batches 5243 -> 5695 GB/s.  PIPE = 4 keeps the whole run: its copy serves
+// short workgroups of 2^7 to 2^10 points, which measured faster with the
+// plain copy (binary16 2^9 6489 against 6197 GB/s, 2^10 6198 against 6040).
+constexpr bool compact_copy(int enc, int pipe) { return is_quarter(enc) && pipe != 4; }
+constexpr int quarter_slot(int c) {
+    if (c < 2) return 0;
+    int top = 1;
+    while (2 * top <= c) top *= 2;
+    return c - top / 2;
+}
+template <class PP>
+constexpr int quarter_copy_offset(int pass) {
+    int n = 0;
+    for (int p = 1; p < pass; ++p) n += 1 << (PP::log_l0(p) + PP::lr(p) - 1);
+    return n;
+}
+template <int LOG_NU, int LOG_E, int MODE, int LANE, class PP, int PIPE, int ENC = ENC_TABLE>
 constexpr int lds_twiddle_entries() {
     constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PP, PIPE>();
     if (LAST == 0) return 0;
+    if (compact_copy(ENC, PIPE)) return quarter_copy_offset<PP>(LAST + 1);
     return (1 << (PP::log_l0(LAST) + PP::lr(LAST))) - (1 << PP::log_l0(1));
 }
 // Row units (PIPE = 3): the first pass of row q0 takes entries
 // q0 + c 2^log_m, 1 <= c < R0, the same for the G lanes of the unit; the
-// workgroup copies entry (c, unit) to LDS slot (c - 1) UPW + unit.
-template <int MODE, int UPW, class PP, int PIPE>
+// workgroup copies entry (c, unit) to LDS slot row_slot(c) UPW + unit.
+constexpr int row_slot(int enc, int c) { return is_quarter(enc) ? quarter_slot(c) : c - 1; }
+template <int MODE, int UPW, class PP, int PIPE, int ENC = ENC_TABLE>
 constexpr int lds_row_twiddle_entries() {
-    return (MODE == MODE_ROWS && PIPE == 3) ? ((1 << PP::lr(0)) - 1) * UPW : 0;
+    if (MODE != MODE_ROWS || PIPE != 3) return 0;
+    return (is_quarter(ENC) ? (1 << PP::lr(0)) / 2 : (1 << PP::lr(0)) - 1) * UPW;
 }
 // Byte offset of the twiddle copy: the exchange area rounded up to 16 bytes.
 template <class E, int LOG_E, int MODE, int UPW, class PP>
@@ -764,8 +788,8 @@ constexpr size_t lds_twiddle_offset() {
 // LDS bytes of a workgroup: the exchange area, and with PIPE = 3, 4 or 5 the twiddle copy.
 template <class E, int LOG_NU, int LOG_E, int MODE, int UPW, int LANE, int PIPE, class PP, int ENC = ENC_TABLE>
 constexpr size_t unit_lds_bytes() {
-    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PP, PIPE>() +
-                       lds_row_twiddle_entries<MODE, UPW, PP, PIPE>();
+    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PP, PIPE, ENC>() +
+                       lds_row_twiddle_entries<MODE, UPW, PP, PIPE, ENC>();
     if (TE == 0) return unit_lds_elems<E, LOG_E, MODE, UPW, PP>() * sizeof(E);
     return lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>() + (size_t)TE * sizeof(TwT<E, ENC>);
 }
@@ -1291,15 +1315,22 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                 const TW* ltw = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) +
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
                 const int q = (g + G * u) >> LOGM;
+                if constexpr (compact_copy(PENC, Geo::kTwiddleLds)) {
+                    ltw += quarter_copy_offset<PP>(P);
 #pragma unroll
-                for (int c = 1; c < R; ++c)
-                    if (quarter_loads(PENC, c)) tw[c] = ltw[q + L0 * c - L01];
+                    for (int c = 1; c < R; ++c)
+                        if (quarter_loads(PENC, c)) tw[c] = ltw[q + L0 * quarter_slot(c)];
+                } else {
+#pragma unroll
+                    for (int c = 1; c < R; ++c)
+                        if (quarter_loads(PENC, c)) tw[c] = ltw[q + L0 * c - L01];
+                }
             } else if constexpr (P == 0 && MODE == MODE_ROWS && Geo::kTwiddleLds == 3) {
                 const TW* ltw = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) +
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
 #pragma unroll
                 for (int c = 1; c < R; ++c)
-                    if (quarter_loads(PENC, c)) tw[c] = ltw[(c - 1) * UPW + ul0];
+                    if (quarter_loads(PENC, c)) tw[c] = ltw[row_slot(PENC, c) * UPW + ul0];
             } else if constexpr (TWX) {
                 const TW* ltp = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) -
                                                             (size_t)TPX * sizeof(TW));
@@ -1623,12 +1654,14 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
             // its loads, so a barrier publishes them
             using PPT = PassPlan<LOG_NU, LR0, LR1, LR2, LANE>;
             using TW = TwT<E, ENC>;
-            constexpr int TE = lds_row_twiddle_entries<MODE, UPW, PPT, PIPE>();
+            constexpr int TE = lds_row_twiddle_entries<MODE, UPW, PPT, PIPE, ENC>();
             constexpr int NT = (UPW / UPL) << (LOG_NU - LOG_E);
             TW* dst = reinterpret_cast<TW*>(lds_raw + lds_twiddle_offset<E, LOG_E, MODE, UPW, PPT>());
             const int64_t ublk = (int64_t)blockIdx.x * UPW;
             for (int i = (int)threadIdx.x; i < TE; i += NT) {
-                const int c = 1 + i / UPW, ul = i % UPW;
+                // slot k holds c = k + 1, with quarter symmetry c = k + 2^floor(log2 k) (1 for k = 0)
+                const int k = i / UPW, ul = i % UPW;
+                const int c = !is_quarter(ENC) ? k + 1 : (k == 0 ? 1 : k + (1 << (31 - __builtin_clz((unsigned)k))));
                 const UnitGeom geo = unit_geom<LOG_NU, MODE>(ublk + ul, log_m);   // q0 < 2^log_m
                 dst[i] = lt[geo.q0 + ((int64_t)c << geo.log_lb)];
             }
@@ -1640,14 +1673,33 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
             // pass 1 reads it
             using PPT = PassPlan<LOG_NU, LR0, LR1, LR2, LANE>;
             using TW = TwT<E, ENC>;
-            constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE>();
+            constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE, ENC>();
             constexpr int CHUNKS = (int)(TE * sizeof(TW) / 16);
             constexpr int NT = (UPW / UPL) << (LOG_NU - LOG_E);
             static_assert(TE > 0 && (TE * sizeof(TW)) % 16 == 0 && ((1 << LR0) * sizeof(TW)) % 16 == 0,
                           "LDS twiddles: whole 16-byte chunks from a 16-byte aligned start");
-            const uint4* src = reinterpret_cast<const uint4*>(lt + (1 << LR0));
             uint4* dst = reinterpret_cast<uint4*>(lds_raw + lds_twiddle_offset<E, LOG_E, MODE, UPW, PPT>());
-            for (int i = (int)threadIdx.x; i < CHUNKS; i += NT) dst[i] = src[i];
+            if constexpr (compact_copy(ENC, PIPE)) {
+                // pass by pass: entry k of its part is table entry k + L0 for
+                // k < L0 and k + L0 2^floor(log2(k / L0)) beyond
+                constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE>();
+                constexpr int PER = 16 / (int)sizeof(TW);       // entries of a chunk
+                const uint4* src = reinterpret_cast<const uint4*>(lt);
+#pragma unroll
+                for (int p = 1; p <= LAST; ++p) {
+                    const int ll0 = PPT::log_l0(p);
+                    const int n = (1 << (ll0 + PPT::lr(p) - 1)) / PER;
+                    uint4* d = dst + quarter_copy_offset<PPT>(p) / PER;
+                    for (int i = (int)threadIdx.x; i < n; i += NT) {
+                        const unsigned h = (unsigned)(i * PER) >> ll0;
+                        const int skip = h == 0 ? 1 : 1 << (31 - __builtin_clz(h));
+                        d[i] = src[i + (skip << ll0) / PER];
+                    }
+                }
+            } else {
+                const uint4* src = reinterpret_cast<const uint4*>(lt + (1 << LR0));
+                for (int i = (int)threadIdx.x; i < CHUNKS; i += NT) dst[i] = src[i];
+            }
         }
         // PIPE = 5: the middle pass from LDS (as PIPE = 3) and the last pass's
         // twiddles prefetched a pass ahead (as PIPE = 2)
