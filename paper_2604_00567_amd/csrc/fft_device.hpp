@@ -101,8 +101,10 @@ __device__ __forceinline__ void bfly(f2_t& a, f2_t& b, const TwF tw) {
 // rotate of the packed pair by 16 bits, and each widening, which is exact,
 // folds into its FMA (v_fma_mix_f32), so the FMAs, their operands and their
 // roundings are those of widening first and calling bfly.
+// COS: the entry is known to be on the cosine path.
+template <bool COS>
 __device__ __forceinline__ void bfly_stored(uint32_t a, uint32_t b, const TwF tw, f2_t& A, f2_t& B) {
-    const uint32_t c = __builtin_amdgcn_alignbit(b, b, tw.mask & 16u);
+    const uint32_t c = COS ? b : __builtin_amdgcn_alignbit(b, b, tw.mask & 16u);
     const float cr = (float)__builtin_bit_cast(_Float16, (uint16_t)c);
     const float ci = (float)__builtin_bit_cast(_Float16, (uint16_t)(c >> 16));
     const float ar = (float)__builtin_bit_cast(_Float16, (uint16_t)a);
@@ -144,7 +146,46 @@ __device__ __forceinline__ void bfly_stored(uint32_t a, uint32_t b, const TwF tw
 //               2^16 3309 -> 3593 GB/s; binary32 2^14 4461 -> 4788; binary16
 //               storage with binary32 butterflies 2^10 4443 -> 5063 GB/s.
 enum { ENC_TABLE = 0, ENC_SELECT = 1, ENC_BRANCH = 2, ENC_RADIX4 = 3, ENC_QUARTER = 4, ENC_QUARTER_INV = 5 };
+//   ENC_PATHS   the butterflies of a first pass whose table is a dual-select one:
+//               the path of each entry is known when compiled (path_is_sine).
+enum { ENC_PATHS = 6 };
 constexpr bool is_quarter(int enc) { return enc == ENC_QUARTER || enc == ENC_QUARTER_INV; }
+
+// Whether dual-select puts W_L^j (L = 2^log_l) on the sine path (Sec. V's index
+// rule: cosine for 8 j <= L or 8 j > 3 L).  Checked on every table whose kernels
+// use it (quarter_symmetric).
+constexpr bool path_is_sine(int log_l, int j) { return 8 * j > (1 << log_l) && 8 * j <= 3 << log_l; }
+
+// The butterfly on a known path: the operand order is that of the operands, no
+// rotate or select (a quarter of the binary16 butterfly's instructions, and of
+// the binary32 one's).
+template <bool SINE>
+__device__ __forceinline__ void bfly_path(uint32_t& a, uint32_t& b, const TwH tw) {
+    const h2_t bv = as_h2(b);
+    const h2_t cv = SINE ? bv.yx : bv;
+    const h2_t tv = as_h2(tw.ts);
+    const h2_t w = as_h2(tw.w);
+    const h2_t av = as_h2(a);
+    h2_t tt;
+    tt.x = -tv.y;
+    tt.y = tv.y;
+    const h2_t s = __builtin_elementwise_fma(tt, cv.yx, cv);
+    a = as_u32(__builtin_elementwise_fma(s, w, av));
+    b = as_u32(__builtin_elementwise_fma(-s, w, av));
+}
+template <bool SINE>
+__device__ __forceinline__ void bfly_path(f2_t& a, f2_t& b, const TwF tw) {
+    const float cr = SINE ? b.y : b.x, ci = SINE ? b.x : b.y;
+    const float s1 = __builtin_fmaf(-tw.t, ci, cr);
+    const float s2 = __builtin_fmaf(tw.t, cr, ci);
+    f2_t A, B;
+    A.x = __builtin_fmaf(s1, tw.sm, a.x);
+    A.y = __builtin_fmaf(s2, tw.m, a.y);
+    B.x = __builtin_fmaf(-s1, tw.sm, a.x);
+    B.y = __builtin_fmaf(-s2, tw.m, a.y);
+    a = A;
+    b = B;
+}
 
 template <int ENC>
 __device__ __forceinline__ void bfly_enc(uint32_t& a, uint32_t& b, const TwH tw) {
@@ -636,6 +677,9 @@ __device__ __forceinline__ void reg_pass(E* v, const TW* tw, uint32_t fix = 0) {
                                 a, b, e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
                         else
                             bfly(a, b, tw[c]);
+                    } else if constexpr (ENC == ENC_PATHS) {
+                        if (path_is_sine(t, e)) bfly_path<true>(a, b, tw[c]);
+                        else bfly_path<false>(a, b, tw[c]);
                     } else {
                         bfly_enc<ENC>(a, b, tw[c]);
                     }
@@ -1295,8 +1339,8 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
 
         // Quarter symmetry serves the passes whose entries depend on the lane; a
         // first pass with its own table offsets reads the same few entries on
-        // every lane (scalar loads).
-        constexpr int PENC = is_quarter(Geo::kEncoding) && P == 0 && MODE != MODE_ROWS ? (int)ENC_TABLE
+        // every lane (scalar loads), whose paths are known.
+        constexpr int PENC = is_quarter(Geo::kEncoding) && P == 0 && MODE != MODE_ROWS ? (int)ENC_PATHS
                                                                                       : Geo::kEncoding;
         uint32_t fix_bits = 0;
         if constexpr (is_quarter(PENC)) fix_bits = quarter_fix_bits(lt);
@@ -1354,7 +1398,7 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                     E* vg = v + k * EL + u * R;
                     const uint32_t* rg = raw + k * EL + u * R;
 #pragma unroll
-                    for (int i = 0; i < R / 2; ++i) bfly_stored(rg[i], rg[i + R / 2], tw[1], vg[i], vg[i + R / 2]);
+                    for (int i = 0; i < R / 2; ++i) bfly_stored<PENC == ENC_PATHS>(rg[i], rg[i + R / 2], tw[1], vg[i], vg[i + R / 2]);
                     reg_pass<LR, PENC, ODD, 2>(vg, tw, fix);
                 }
             } else {
@@ -1571,11 +1615,24 @@ __device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk) {
     return b / group * group + b % 8 * kColumnRun + b % group / 8;
 }
 
+// Waves per SIMD that the compiler is asked to leave registers for: 4 where a
+// whole transform stored in binary16 and computed in binary32 holds 32 elements per
+// lane and its LDS lets as many run (2^13: 128 registers instead of 134, four
+// workgroups per CU instead of three), else no request.
+template <class E, class S, int LOG_NU, int LOG_E, int UPW, int MODE, int LANE, int PIPE, int ENC, class PP>
+constexpr int mixed_waves() {
+    if (std::is_same_v<E, S> || MODE != MODE_SMALL || LOG_E != 5) return 1;
+    constexpr size_t lds = unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PP, ENC>();
+    return (int)(kLdsBytes / lds) * (UPW << (LOG_NU - LOG_E)) >= 4 * 4 * 64 ? 4 : 1;
+}
+
 // SI, SO: storage types of the input and output (E unless the plan stores
 // binary16 and computes in binary32).
 template <class E, int LOG_NU, int LOG_E, int UPW, int UPL, int MODE, int LR0, int LR1, int LR2, int STG,
           int LANE, int PIPE, class SI = E, class SO = E, int ENC = ENC_TABLE>
 __global__ void __launch_bounds__((UPW / UPL) << (LOG_NU - LOG_E))
+__attribute__((amdgpu_waves_per_eu((mixed_waves<E, SI, LOG_NU, LOG_E, UPW, MODE, LANE, PIPE, ENC,
+                                                PassPlan<LOG_NU, LR0, LR1, LR2, LANE>>()))))
 fft_unit_kernel(const SI* in, SO* out, const TwT<E, ENC>* __restrict__ lt, int64_t units, int log_m) {
     unit_kernel_body<E, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, SI, SO, ENC>(
         in, out, lt, units, log_m);
