@@ -156,6 +156,16 @@ constexpr bool is_quarter(int enc) { return enc == ENC_QUARTER || enc == ENC_QUA
 // use it (quarter_symmetric).
 constexpr bool path_is_sine(int log_l, int j) { return 8 * j > (1 << log_l) && 8 * j <= 3 << log_l; }
 
+// The path of the entries j = q + L0 e (every column q < L0) of stage t, span
+// L = L0 2^t, in its first quarter: with L/8 = L0 2^(t-3) a multiple of L0, they lie
+// on one side of it for all q, except that j = L/8 itself (q = 0) is on the cosine
+// path with those below.
+enum { PATH_TABLE = 0, PATH_COSINE = 1, PATH_SINE = 2 };
+constexpr int quarter_path(int t, int e) {
+    if (t < 3 || e == (1 << t) >> 3) return PATH_TABLE;
+    return e < (1 << t) >> 3 ? PATH_COSINE : PATH_SINE;
+}
+
 // The butterfly on a known path: the operand order is that of the operands, no
 // rotate or select (a quarter of the binary16 butterfly's instructions, and of
 // the binary32 one's).
@@ -250,9 +260,12 @@ __device__ __forceinline__ void bfly_enc(f2_t& a, f2_t& b, const TwF tw) {
 // j but 0, where the ratios of W^0 and W^(L/4) are a zero and cot(pi/2) as FP64
 // evaluates it, the same two values at every level: the caller corrects t there
 // (quarter_fix).
-template <bool INV>
+// PATH: the path of tw where it is known when compiled (quarter_path).
+template <bool INV, int PATH>
 __device__ __forceinline__ void bfly_quarter(uint32_t& a, uint32_t& b, const TwH tw) {
-    const h2_t cv = as_h2(__builtin_amdgcn_alignbit(b, b, tw.ts));
+    const h2_t bv = as_h2(b);
+    const h2_t cv = PATH == PATH_TABLE ? as_h2(__builtin_amdgcn_alignbit(b, b, tw.ts))
+                                       : (PATH == PATH_SINE ? bv.yx : bv);
     const h2_t tv = as_h2(tw.ts);
     const h2_t w = as_h2(tw.w);
     const h2_t av = as_h2(a);
@@ -267,13 +280,16 @@ __device__ __forceinline__ void bfly_quarter(uint32_t& a, uint32_t& b, const TwH
     a = as_u32(INV ? Q : P);
     b = as_u32(INV ? P : Q);
 }
-template <bool INV>
+template <bool INV, int PATH>
 __device__ __forceinline__ void bfly_quarter(f2_t& a, f2_t& b, const TwF tw) {
     const float bxf = b.x, byf = b.y;
-    const uint32_t br = __builtin_bit_cast(uint32_t, bxf);
-    const uint32_t bi = __builtin_bit_cast(uint32_t, byf);
-    const float cr = __builtin_bit_cast(float, (tw.mask & bi) | (~tw.mask & br));
-    const float ci = __builtin_bit_cast(float, (tw.mask & br) | (~tw.mask & bi));
+    float cr = PATH == PATH_SINE ? byf : bxf, ci = PATH == PATH_SINE ? bxf : byf;
+    if constexpr (PATH == PATH_TABLE) {
+        const uint32_t br = __builtin_bit_cast(uint32_t, bxf);
+        const uint32_t bi = __builtin_bit_cast(uint32_t, byf);
+        cr = __builtin_bit_cast(float, (tw.mask & bi) | (~tw.mask & br));
+        ci = __builtin_bit_cast(float, (tw.mask & br) | (~tw.mask & bi));
+    }
     const float s1 = __builtin_fmaf(-tw.t, ci, cr);
     const float s2 = __builtin_fmaf(tw.t, cr, ci);
     f2_t P, Q;
@@ -650,9 +666,11 @@ __device__ __forceinline__ void reg_pass4(E* v, const TW* tw) {
 }
 
 // T0 > 1: stages before T0 are done already (a binary16-storage first pass).
+// PATHS: with quarter symmetry, the operand order of entries whose path is known
+// for every column comes from quarter_path.
 // fix: with quarter symmetry, the correction of t in the butterfly that takes
 // entry 0 of its stage for W^(L/4): quarter_fix_bits in column 0, else 0.
-template <int LR, int ENC = ENC_TABLE, bool ODD = false, int T0 = 1, class E, class TW>
+template <int LR, int ENC = ENC_TABLE, bool ODD = false, int T0 = 1, bool PATHS = true, class E, class TW>
 __device__ __forceinline__ void reg_pass(E* v, const TW* tw, uint32_t fix = 0) {
     if constexpr (ENC == ENC_RADIX4) {
         static_assert(T0 == 1, "radix-4 passes start at their first stage");
@@ -671,12 +689,20 @@ __device__ __forceinline__ void reg_pass(E* v, const TW* tw, uint32_t fix = 0) {
                     E b = v[i + H + 2 * H * e];
                     const int c = (1 << (t - 1)) + e;
                     if constexpr (is_quarter(ENC)) {
+                        constexpr bool INV = ENC == ENC_QUARTER_INV;
                         const int q4 = (1 << t) >> 2;    // entries of a quarter of the span
-                        if (t > 1 && e >= q4)
-                            bfly_quarter<ENC == ENC_QUARTER_INV>(
-                                a, b, e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
-                        else
-                            bfly(a, b, tw[c]);
+                        const bool second = t > 1 && e >= q4;
+                        const int path = PATHS ? quarter_path(t, second ? e - q4 : e) : (int)PATH_TABLE;
+                        const TW w = !second ? tw[c] : (e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
+                        if (second) {
+                            if (path == PATH_SINE) bfly_quarter<INV, PATH_SINE>(a, b, w);
+                            else if (path == PATH_COSINE) bfly_quarter<INV, PATH_COSINE>(a, b, w);
+                            else bfly_quarter<INV, PATH_TABLE>(a, b, w);
+                        } else {
+                            if (path == PATH_SINE) bfly_path<true>(a, b, w);
+                            else if (path == PATH_COSINE) bfly_path<false>(a, b, w);
+                            else bfly(a, b, w);
+                        }
                     } else if constexpr (ENC == ENC_PATHS) {
                         if (path_is_sine(t, e)) bfly_path<true>(a, b, tw[c]);
                         else bfly_path<false>(a, b, tw[c]);
@@ -1342,6 +1368,12 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
         // every lane (scalar loads), whose paths are known.
         constexpr int PENC = is_quarter(Geo::kEncoding) && P == 0 && MODE != MODE_ROWS ? (int)ENC_PATHS
                                                                                       : Geo::kEncoding;
+        // Known paths in later passes too (quarter_path): they take the rotates and
+        // selects out (2^10 on binary16 storage 723 -> 707 vector instructions, 108.3 ->
+        // 107.3 us for 65536; a serving slot's step 111.1 -> 110.0), except in binary32
+        // column and row units, whose memory schedule got slower with them (2^20 x 64:
+        // 430 -> 449 us).
+        constexpr bool PATHS = MODE == MODE_SMALL || sizeof(E) == 4;
         uint32_t fix_bits = 0;
         if constexpr (is_quarter(PENC)) fix_bits = quarter_fix_bits(lt);
 
@@ -1399,11 +1431,11 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                     const uint32_t* rg = raw + k * EL + u * R;
 #pragma unroll
                     for (int i = 0; i < R / 2; ++i) bfly_stored<PENC == ENC_PATHS>(rg[i], rg[i + R / 2], tw[1], vg[i], vg[i + R / 2]);
-                    reg_pass<LR, PENC, ODD, 2>(vg, tw, fix);
+                    reg_pass<LR, PENC, ODD, 2, PATHS>(vg, tw, fix);
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < UPL; ++k) reg_pass<LR, PENC, ODD>(v + k * EL + u * R, tw, fix);
+                for (int k = 0; k < UPL; ++k) reg_pass<LR, PENC, ODD, 1, PATHS>(v + k * EL + u * R, tw, fix);
             }
         }
         if constexpr (PFN) {

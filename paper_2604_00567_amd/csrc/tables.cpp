@@ -129,7 +129,7 @@ bool quarter_symmetric(const std::vector<uint8_t>& img, int64_t ncap, int dtype,
         return Bits{u[0], u[1], u[2], u[3] != 0};
     };
     if (ncap < 4) return false;
-    for (int64_t L = 2; L <= ncap && L <= 64; L <<= 1)
+    for (int64_t L = 2; L <= ncap; L <<= 1)
         for (int64_t j = 0; j < L / 2; ++j)
             if (entry(L / 2 + j).sine != (8 * j > L && 8 * j <= 3 * L)) return false;
     const uint32_t t0 = entry(2).t, t1 = entry(3).t;

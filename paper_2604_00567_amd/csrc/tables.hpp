@@ -35,8 +35,8 @@ std::vector<uint8_t> build_level_table(int64_t ncap, int dtype, int kind, bool i
 // (j < L/4) is on the other path with multipliers (sigma' m', m') =
 // (m, -sigma m) (inverse: (-m, sigma m)) and, for j > 0, ratio -t; the ratios
 // of j = 0 and j = L/4 are the same two values at every level.  Also that the
-// levels up to 64 (a first pass's) have dual-select's paths: sine exactly
-// for L < 8 j <= 3 L (path_is_sine in fft_device.hpp).
+// paths are dual-select's: sine exactly for L < 8 j <= 3 L (path_is_sine and
+// quarter_path in fft_device.hpp).
 bool quarter_symmetric(const std::vector<uint8_t>& img, int64_t ncap, int dtype, bool inverse);
 
 // Radix-4 form (Sec. VI, generality): the butterfly of span L and column j
