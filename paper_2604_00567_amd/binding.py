@@ -367,17 +367,22 @@ def fft_serve_slot_destroy(slot: int) -> None:
 
 # ----------------------------------------------------------- torch marshalling
 
+# The handle of torch.cuda.current_stream(), without the Stream object that the
+# call builds: 0.16 us instead of 2.9, of the 7.2 us that a Plan.execute of a few
+# small transforms took on the host (4.7 now; the launch itself is 3.0).
+def _current_stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _torch_stream(stream) -> int:
-    import torch
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
 def _check_tensor(t, n: int, batch: int, dt: int):
-    import torch
     f16_stored = dt in (FFT_F16, FFT_F16_F32)
     want = torch.float16 if f16_stored else torch.float32
     if not t.is_cuda:
