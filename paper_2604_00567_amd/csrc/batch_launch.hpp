@@ -72,6 +72,10 @@ const void* batch_list_func(int list, bool quarter);
 hipError_t launch_batch_list(int list, bool quarter, const void* in, void* out, const void* lt,
                              const int64_t* offs, int64_t count, hipStream_t s);
 
+// Copies a work list of `bytes` (rounded up to 16) from pinned host memory to the
+// device buffer dst, both 16-byte aligned, with a kernel.
+hipError_t launch_stage_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
+
 // Queue words per batch or serving slot: (head, workgroups done) for each of
 // the two phases; zero when allocated, and left zero by every launch.
 constexpr int kQueueWords = 4;

@@ -1,8 +1,8 @@
 // Serving slots: one in-flight launch of the persistent batch kernels over the
 // requests admitted in one scheduling step.  The work list is built on the
 // host, packed with the transform offsets into one pinned staging buffer and
-// copied to the slot's device buffer with one copy on the slot's stream, so
-// a step costs one copy and one launch per phase, and consecutive steps on
+// copied to the slot's device buffer by a kernel on the slot's stream, so
+// a step costs one small launch and one per phase, and consecutive steps on
 // different slots overlap on the device.
 #include <hip/hip_runtime.h>
 
@@ -72,7 +72,8 @@ fft_serve_slot* fft_serve_slot_create(fft_dtype dtype, fft_table_kind kind, int6
     hipError_t e = hipGetDevice(&s->device);
     if (e != hipSuccess) { hip_error(e, "hipGetDevice"); return nullptr; }
     if (get_table(int64_t(1) << 18, s->dtype, s->kind, false, &s->table) != FFT_OK) return nullptr;
-    const size_t stage = sizeof(HostBatchItem) * max_items + sizeof(int64_t) * max_transforms;
+    // whole 16-byte chunks (launch_stage_copy)
+    const size_t stage = (sizeof(HostBatchItem) * max_items + sizeof(int64_t) * max_transforms + 15) / 16 * 16;
     if ((e = hipMalloc(&s->d_stage, stage)) != hipSuccess ||
         (e = hipMalloc(&s->d_ctl, sizeof(unsigned) * kQueueWords)) != hipSuccess ||
         (ws_bytes && (e = hipMalloc(&s->ws, ws_bytes)) != hipSuccess) ||
@@ -134,9 +135,8 @@ int fft_serve_slot_launch(fft_serve_slot* s, const int64_t* n, const int64_t* ba
     std::memcpy(s->h_stage, s->items.data(), ib);
     std::memcpy(s->h_stage + ib, s->offs.data(), ob);
     std::memcpy(s->h_stage + ib + ob, s->lists.data(), bb);
-    if ((e = hipMemcpyAsync(s->d_stage, s->h_stage, ib + ob + bb, hipMemcpyHostToDevice, st)) !=
-        hipSuccess)
-        return hip_error(e, "hipMemcpyAsync(work list)");
+    if ((e = launch_stage_copy(s->h_stage, s->d_stage, ib + ob + bb, st)) != hipSuccess)
+        return hip_error(e, "launch(work list copy)");
     const int64_t* d_lists = (const int64_t*)(s->d_stage + ib + ob);
     for (int i = 0; i < kNumLists; ++i) {
         if (s->nlist[i] && (e = launch_batch_list(i, s->table->quarter, data, data, s->table->ptr, d_lists, s->nlist[i], st)) !=
