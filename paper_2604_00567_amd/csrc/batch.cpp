@@ -322,22 +322,28 @@ static hipKernelNodeParams list_params(const fft_batch* b, ListArgs& a, int list
     return kp;
 }
 
-// Builds the graph once: the list kernels (those with transforms) and phase 0
-// as independent roots (they touch disjoint transforms, so each can fill the
-// others' tails), then phase 1 after phase 0 (each phase a persistent kernel
-// whose workgroups only claim items from a queue, so sharing the device with
-// the list kernels never blocks them).
+// Builds the graph once, two branches over disjoint transforms, so that each can
+// fill the other's tails: the list kernels (those with transforms) one after the
+// other, and phase 0, then phase 1 (each phase a persistent kernel whose
+// workgroups only claim items from a queue, so sharing the device with the list
+// kernels never blocks them).  A replay starts its branches one after the other,
+// the third 36 us after the first: with a branch for each list kernel, the
+// uneven batch of 4096 binary16 transforms of 2^6 .. 2^16 points takes 115 us, with
+// the two in one branch 108 (2^15 points first 118; phase 0 added first 134).
 static int build_graph(fft_batch* b, const void* in, void* out) {
     hipError_t e;
     if ((e = hipGraphCreate(&b->graph, 0)) != hipSuccess) return hip_error(e, "hipGraphCreate");
+    hipGraphNode_t prev = nullptr;
     for (int i = 0; i < kNumLists; ++i) {
         if (b->nlist[i] == 0) continue;
         ListArgs la(b, in, out, i);
         hipKernelNodeParams kp = list_params(b, la, i);
-        if ((e = hipGraphAddKernelNode(&b->lnode[i], b->graph, nullptr, 0, &kp)) != hipSuccess)
+        if ((e = hipGraphAddKernelNode(&b->lnode[i], b->graph, prev ? &prev : nullptr, prev ? 1 : 0, &kp)) !=
+            hipSuccess)
             return hip_error(e, "hipGraphAddKernelNode(list)");
+        prev = b->lnode[i];
     }
-    hipGraphNode_t prev = nullptr;
+    prev = nullptr;
     for (int ph = 0; ph < 2; ++ph) {
         PhaseArgs a(b, in, out, ph);
         if (a.nitems == 0) continue;
@@ -378,9 +384,9 @@ static int retarget(fft_batch* b, const void* in, void* out) {
 // Batches of up to kDirectElems elements launch their kernels one after the other
 // on the caller's stream; larger ones replay a graph whose list kernels and phase
 // 0 fill each other's tails.  A replay costs 20 us of launching with one node and
-// 50 us and more with three branches: binary16, 2^6 .. 2^16 points, 20
+// 50 us and more with a branch for each kernel: binary16, 2^6 .. 2^16 points, 20
 // transforms 69 us by graph and 21 in order, 300 68 and 30, 2000 (25 M
-// elements) 77 and 65, 4096 (48 M) 118 and 127.  In order, a short list (as for
+// elements) 77 and 65, 4096 (48 M) 118 and 127 (108 with two branches).  In order, a short list (as for
 // plans, split_limit) runs split through the output unless the call is in place.
 constexpr int64_t kDirectElems = int64_t(1) << 25;
 static int launch_direct(fft_batch* b, const void* in, void* out, hipStream_t s) {
