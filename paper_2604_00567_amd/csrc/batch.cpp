@@ -322,17 +322,23 @@ static hipKernelNodeParams list_params(const fft_batch* b, ListArgs& a, int list
     return kp;
 }
 
-// Builds the graph once, two branches over disjoint transforms, so that each can
-// fill the other's tails: the list kernels (those with transforms) one after the
-// other, and phase 0, then phase 1 (each phase a persistent kernel whose
-// workgroups only claim items from a queue, so sharing the device with the list
-// kernels never blocks them).  A replay starts its branches one after the other,
-// the third 36 us after the first: with a branch for each list kernel, the
-// uneven batch of 4096 binary16 transforms of 2^6 .. 2^16 points takes 115 us, with
-// the two in one branch 108 (2^15 points first 118; phase 0 added first 134).
+// Builds the graph once: the list kernels (those with transforms) and phase 0 as
+// independent branches (they touch disjoint transforms, so each can fill the
+// others' tails), then phase 1 after phase 0 (each phase a persistent kernel
+// whose workgroups only claim items from a queue, so sharing the device with
+// the list kernels never blocks them).  A replay starts its branches one after the
+// other, the third 36 us after the first; so the 2^15 list follows the 2^16 one in
+// one branch, where the second round of 2^16 workgroups (one per compute unit) still
+// finds room: two branches share the compute units that the first round frees
+// equally, and phase 0's workgroups stay until its queue is empty.  Up to half a
+// round it does: 4096 transforms of 2^6 .. 2^16 points, 256 compute units, branch for
+// each / lists in one, in us: 370 of 2^16 points 120.4 / 111.0, 379 116.9 / 109.9, 393
+// 120.5 / 126.5, 405 123.4 / 127.7; other batches with 177 258.2 / 250.4, 296 100.0
+// / 98.8, 440 135.6 / 147.4, 587 158.5 / 175.0.
 static int build_graph(fft_batch* b, const void* in, void* out) {
     hipError_t e;
     if ((e = hipGraphCreate(&b->graph, 0)) != hipSuccess) return hip_error(e, "hipGraphCreate");
+    const bool lists_in_one = 2 * b->nlist[0] <= 3 * (int64_t)b->cus;
     hipGraphNode_t prev = nullptr;
     for (int i = 0; i < kNumLists; ++i) {
         if (b->nlist[i] == 0) continue;
@@ -341,7 +347,7 @@ static int build_graph(fft_batch* b, const void* in, void* out) {
         if ((e = hipGraphAddKernelNode(&b->lnode[i], b->graph, prev ? &prev : nullptr, prev ? 1 : 0, &kp)) !=
             hipSuccess)
             return hip_error(e, "hipGraphAddKernelNode(list)");
-        prev = b->lnode[i];
+        if (lists_in_one) prev = b->lnode[i];
     }
     prev = nullptr;
     for (int ph = 0; ph < 2; ++ph) {
@@ -386,7 +392,7 @@ static int retarget(fft_batch* b, const void* in, void* out) {
 // 0 fill each other's tails.  A replay costs 20 us of launching with one node and
 // 50 us and more with a branch for each kernel: binary16, 2^6 .. 2^16 points, 20
 // transforms 69 us by graph and 21 in order, 300 68 and 30, 2000 (25 M
-// elements) 77 and 65, 4096 (48 M) 118 and 127 (108 with two branches).  In order, a short list (as for
+// elements) 77 and 65, 4096 (48 M) 118 and 127 (110 with the lists in one branch).  In order, a short list (as for
 // plans, split_limit) runs split through the output unless the call is in place.
 constexpr int64_t kDirectElems = int64_t(1) << 25;
 static int launch_direct(fft_batch* b, const void* in, void* out, hipStream_t s) {
