@@ -695,16 +695,25 @@ __device__ __forceinline__ void reg_pass(E* v, const TW* tw, uint32_t fix = 0) {
                         constexpr bool INV = ENC == ENC_QUARTER_INV;
                         const int q4 = (1 << t) >> 2;    // entries of a quarter of the span
                         const bool second = t > 1 && e >= q4;
-                        const int path = PATHS ? quarter_path(t, second ? e - q4 : e) : (int)PATH_TABLE;
-                        const TW w = !second ? tw[c] : (e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
-                        if (second) {
-                            if (path == PATH_SINE) bfly_quarter<INV, PATH_SINE>(a, b, w);
-                            else if (path == PATH_COSINE) bfly_quarter<INV, PATH_COSINE>(a, b, w);
-                            else bfly_quarter<INV, PATH_TABLE>(a, b, w);
+                        if constexpr (!PATHS) {
+                            // a form of its own: folded into the one below the 2^16-point kernel spills
+                            if (second)
+                                bfly_quarter<INV, PATH_TABLE>(a, b,
+                                                              e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
+                            else
+                                bfly(a, b, tw[c]);
                         } else {
-                            if (path == PATH_SINE) bfly_path<true>(a, b, w);
-                            else if (path == PATH_COSINE) bfly_path<false>(a, b, w);
-                            else bfly(a, b, w);
+                            const int path = quarter_path(t, second ? e - q4 : e);
+                            const TW w = !second ? tw[c] : (e == q4 ? quarter_fix(tw[c - q4], fix) : tw[c - q4]);
+                            if (second) {
+                                if (path == PATH_SINE) bfly_quarter<INV, PATH_SINE>(a, b, w);
+                                else if (path == PATH_COSINE) bfly_quarter<INV, PATH_COSINE>(a, b, w);
+                                else bfly_quarter<INV, PATH_TABLE>(a, b, w);
+                            } else {
+                                if (path == PATH_SINE) bfly_path<true>(a, b, w);
+                                else if (path == PATH_COSINE) bfly_path<false>(a, b, w);
+                                else bfly(a, b, w);
+                            }
                         }
                     } else if constexpr (ENC == ENC_PATHS) {
                         if (path_is_sine(t, e)) bfly_path<true>(a, b, tw[c]);
@@ -1375,8 +1384,11 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
         // selects out (2^10 on binary16 storage 723 -> 707 vector instructions, 108.3 ->
         // 107.3 us for 65536; a serving slot's step 111.1 -> 110.0), except in binary32
         // column and row units, whose memory schedule got slower with them (2^20 x 64:
-        // 430 -> 449 us).
-        constexpr bool PATHS = MODE == MODE_SMALL || sizeof(E) == 4;
+        // 430 -> 449 us), and in the last pass of 1024-lane workgroups with 64 elements a
+        // lane, whose 128 registers are full: with them there the binary16 2^16 kernels
+        // kept 20 to 28 bytes a lane in scratch memory, without none (inverse 2^16 x 1024
+        // 142.6 -> 141.2 us, forward the same; uneven batches 0.3 to 1 % faster).
+        constexpr bool PATHS = !(NT_OF == 1024 && LOG_E == 6 && P + 1 == NP) && (MODE == MODE_SMALL || sizeof(E) == 4);
         uint32_t fix_bits = 0;
         if constexpr (is_quarter(PENC)) fix_bits = quarter_fix_bits(lt);
 
