@@ -289,7 +289,8 @@ int fft_config_count(int64_t n, fft_dtype dtype, int* single, int* cols, int* ro
  * the transforms of a short list, with the intermediate in the output, unless
  * the call is in place.  (The kernels leave their work-queue counters at zero
  * for the next execute.)  The batch owns a workspace of the summed sizes of its
- * two-pass transforms; it must not run concurrently on two streams.
+ * two-pass transforms; it must not run concurrently on two streams.  Threads
+ * may share a batch on one stream: each execute is enqueued whole.
  * Returns NULL on error.
  */
 fft_batch* fft_batch_create(const int64_t* n, int64_t count, fft_dtype dtype, fft_table_kind kind);

@@ -62,7 +62,7 @@ struct fft_batch {
     hipGraphExec_t exec = nullptr;
     hipGraphNode_t knode[2] = {nullptr, nullptr};
     hipGraphNode_t lnode[dsfft::kNumLists] = {};   // list kernels (binary16 2^16, 2^15)
-    std::mutex launch_mu;
+    std::mutex launch_mu;                  // batch_execute
     const void* cap_in = nullptr;
     void* cap_out = nullptr;
     ~fft_batch();
@@ -396,8 +396,6 @@ static int retarget(fft_batch* b, const void* in, void* out) {
 // plans, split_limit) runs split through the output unless the call is in place.
 constexpr int64_t kDirectElems = int64_t(1) << 25;
 static int launch_direct(fft_batch* b, const void* in, void* out, hipStream_t s) {
-    // one call's launches stay together: the phases share the batch's workspace
-    std::lock_guard<std::mutex> lock(b->launch_mu);
     hipError_t e = hipSuccess;
     const void* lt = b->table->ptr;
     const bool quarter = b->table->quarter;
@@ -433,6 +431,9 @@ int batch_execute(fft_batch* b, const void* in, void* out, hipStream_t s) {
     if (x != y && x < y + bytes && y < x + bytes)
         return set_error(FFT_EINVAL, "in and out partially overlap");
     if (b->items.empty() && b->lists.empty()) return FFT_OK;
+    // One call at a time: its launches share the batch's workspace and queue words,
+    // and a replay the graph whose nodes the call has just pointed at its buffers.
+    std::lock_guard<std::mutex> lock(b->launch_mu);
     int rc = FFT_OK;
     if (b->total <= kDirectElems) return launch_direct(b, in, out, s);
     if (!b->exec) rc = build_graph(b, in, out);
