@@ -166,7 +166,10 @@ int fft_table_build_dir(int64_t n, fft_dtype dtype, fft_table_kind kind, int dir
  * units per workgroup, register passes of radix 2^r0, 2^r1, 2^r2; S = 1:
  * 16-byte LDS-staged I/O; L = 1: last two stages across lanes; T threads and
  * B bytes of LDS per workgroup), then ",upl=K" when a lane holds K units,
- * ",enc=select" / ",enc=branch" for the path-encoding variants, and for a
+ * ",enc=select" / ",enc=branch" for the path-encoding variants, ",quarter"
+ * where the kernel that runs loads half of each stage's twiddles (B is that
+ * kernel's), "; out of place: split through the output, ..." where calls that
+ * are not in place run as column and row kernels, and for a
  * two-pass plan " | rows:... | chunk=C" (its second kernel, and the
  * transforms per workspace chunk).  P says where
  * twiddles come from besides per-lane table loads: 1 persistent workgroups

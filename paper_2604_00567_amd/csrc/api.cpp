@@ -135,9 +135,17 @@ const KernelCfg* find_plain_kernel(int dtype, int mode, int log_nu, bool radix4 
 // quarter of each stage's twiddles from the first wherever the plan's table
 // holds that symmetry (dual-select tables) and the form is compiled.
 template <class Cfg>
+static LaunchFn quarter_launch(const fft_plan* p, const Cfg* k) {
+    return !p->table->quarter ? nullptr : (p->inverse ? k->launch_quarter_inverse : k->launch_quarter);
+}
+template <class Cfg>
 static LaunchFn plan_launch(const fft_plan* p, const Cfg* k) {
-    const LaunchFn q = p->inverse ? k->launch_quarter_inverse : k->launch_quarter;
-    return p->table->quarter && q ? q : k->launch;
+    const LaunchFn q = quarter_launch(p, k);
+    return q ? q : k->launch;
+}
+// LDS bytes of the form that plan_launch picks.
+static size_t plan_lds(const fft_plan* p, const KernelCfg* k) {
+    return quarter_launch(p, k) ? k->lds_quarter : k->lds_bytes;
 }
 
 int count_kernels(int dtype, int mode, int log_nu, bool radix4) {
@@ -146,18 +154,19 @@ int count_kernels(int dtype, int mode, int log_nu, bool radix4) {
     return n;
 }
 
-std::string describe(const KernelCfg* k) {
+std::string describe(const fft_plan* p, const KernelCfg* k) {
     if (!k) return "none";
     static const char* modes[] = {"small", "cols", "rows"};
     char buf[160];
     std::snprintf(buf, sizeof buf,
                   "%s:nu=2^%d,e=2^%d,upw=%d,r=[%d,%d,%d],stg=%d,lane=%d,pipe=%d,t=%d,lds=%zu",
                   modes[k->mode], k->log_nu, k->log_e, k->upw, k->lr[0], k->lr[1], k->lr[2],
-                  k->staged, k->lane_tail, k->pipelined, k->threads, k->lds_bytes);
+                  k->staged, k->lane_tail, k->pipelined, k->threads, plan_lds(p, k));
     std::string d = buf;
     if (k->upl > 1) d += ",upl=" + std::to_string(k->upl);
     if (k->encoding == ENC_RADIX4) d += ",radix4";
     else if (k->encoding) d += k->encoding == ENC_SELECT ? ",enc=select" : ",enc=branch";
+    else if (quarter_launch(p, k)) d += ",quarter";
     return d;
 }
 
@@ -185,13 +194,13 @@ static int small_limit(int dtype) {
 // may also be wider than the tuned one where that brings the launch down to
 // one round and two workgroups still share a compute unit (binary16 2^17 x 32 19.3
 // -> 17.2 us; with one per compute unit, binary16 2^18 x 32, 25.0 -> 27.3).
-static const KernelCfg* narrow_kernel(const KernelCfg* tuned, int64_t units, int cus) {
+static const KernelCfg* narrow_kernel(const fft_plan* p, const KernelCfg* tuned, int64_t units, int cus) {
     const KernelCfg* best = nullptr;
     for (int v = 0;; ++v) {
         const KernelCfg* k = find_kernel(tuned->dtype, tuned->mode, tuned->log_nu, v);
         if (!k) return best ? best : tuned;
         if (k->staged || k->encoding || (units + k->upw - 1) / k->upw > cus) continue;
-        if (k->upw > tuned->upw && (k->mode == MODE_COLS || 2 * k->lds_bytes > 160 * 1024)) continue;
+        if (k->upw > tuned->upw && (k->mode == MODE_COLS || 2 * plan_lds(p, k) > 160 * 1024)) continue;
         // eight binary16 units of 2^10 points: 32-byte runs of 4 KiB strides, slower than sixteen
         if (k->log_nu >= 10 && k->upw * work_elem_bytes(k->dtype) < 64) continue;
         if (!best || k->upw < best->upw || (k->upw == best->upw && k->launch_quarter && !best->launch_quarter)) best = k;
@@ -249,8 +258,8 @@ static void few_transforms_choice(fft_plan* p) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess) return;
     if (p->k2) {
         const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
-        p->k1 = p->k1_plain = narrow_kernel(p->k1, p->batch << m2, cus);
-        p->k2 = narrow_kernel(p->k2, p->batch << m1, cus);
+        p->k1 = p->k1_plain = narrow_kernel(p, p->k1, p->batch << m2, cus);
+        p->k2 = narrow_kernel(p, p->k2, p->batch << m1, cus);
         return;
     }
     if (p->batch * 16 <= (int64_t)split_limit(p->dtype, p->log_n) * cus) {
@@ -508,11 +517,11 @@ int fft_plan_info(const fft_plan* p, int64_t* n, int64_t* batch, int* dtype, int
     if (dtype) *dtype = p->dtype;
     if (kind) *kind = p->kind;
     if (config_out && cap) {
-        std::string d = describe(p->k1);
+        std::string d = describe(p, p->k1);
         if (p->few_cols)
             d += "; out of place: split through the output, " + std::to_string(p->few_cols->upw) + " columns and " +
                  std::to_string(p->few_rows->upw) + " rows per workgroup";
-        if (p->k2) d += " | " + describe(p->k2) + " | chunk=" + std::to_string(p->chunk);
+        if (p->k2) d += " | " + describe(p, p->k2) + " | chunk=" + std::to_string(p->chunk);
         std::snprintf(config_out, cap, "%s", d.c_str());
     }
     return FFT_OK;

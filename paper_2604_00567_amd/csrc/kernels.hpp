@@ -30,6 +30,7 @@ struct KernelCfg {
     // the same results from about half of the twiddle loads, for tables with
     // quarter symmetry: forward and inverse (null where not compiled)
     LaunchFn launch_quarter, launch_quarter_inverse;
+    size_t lds_quarter;     // LDS bytes of those forms, whose twiddle copies are shorter
     const void* func;
 };
 

@@ -155,6 +155,8 @@ static constexpr LaunchFn launch_quarter() {
                     ENC_QUARTER>(),                                                                   \
      launch_quarter<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC, \
                     ENC_QUARTER_INV>(),                                                               \
+     unit_lds_bytes<ELEM_T, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE,                               \
+                    PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC_QUARTER>(),                     \
      kernel_entry<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC>()},
 #define CFGU(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL)                   \
     CFGE(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL, ENC_TABLE)

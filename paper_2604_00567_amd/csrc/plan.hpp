@@ -28,7 +28,6 @@ int get_table(int64_t n, int dtype, int kind, bool inverse, std::shared_ptr<Devi
 // of the radix-2 butterflies (radix4 = false) or of the radix-4 form.
 const KernelCfg* find_kernel(int dtype, int mode, int log_nu, int variant, bool radix4 = false);
 int count_kernels(int dtype, int mode, int log_nu, bool radix4 = false);
-std::string describe(const KernelCfg* k);
 int elem_bytes(int dtype);
 int work_elem_bytes(int dtype);
 
@@ -63,6 +62,8 @@ fft_plan* plan_create(int64_t n, int64_t batch, int dtype, int kind, const int* 
 constexpr size_t kMaxWorkspaceBytes = (size_t)128 << 20;
 bool tuned_choice(int dtype, int log_n, int* variants);
 int plan_execute(fft_plan* p, const void* in, void* out, hipStream_t s);
+// Text of configuration k as plan p launches it (fft_plan_info, tuner report).
+std::string describe(const fft_plan* p, const KernelCfg* k);
 // Frees a plan-owned workspace after the plan's device is idle.
 void release_workspace(fft_plan* p);
 // Argument checks of an execute (null, alignment, partial overlap).

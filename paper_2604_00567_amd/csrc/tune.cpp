@@ -225,7 +225,7 @@ int fft_tune(int64_t n, int64_t batch, fft_dtype dtype, fft_table_kind kind, int
         char buf[320];
         std::snprintf(buf, sizeof buf, "%s{\"variant\":[%d,%d,%d],\"ms\":%.5f,\"GBs\":%.1f,\"bit_exact\":%s,\"config\":\"%s\"}",
                       rep.size() > 1 ? "," : "", v[0], v[1], v[2], ms, gbs, same ? "true" : "false",
-                      (describe(p->k1) + (p->k2 ? " | " + describe(p->k2) : std::string())).c_str());
+                      (describe(p, p->k1) + (p->k2 ? " | " + describe(p, p->k2) : std::string())).c_str());
         rep += buf;
         if (ok && same && ms > 0) {
             ++accepted;
