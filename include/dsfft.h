@@ -93,8 +93,9 @@ const char* fft_last_error(void);
  * theta = -(2 pi k)/N, cos/sin, the |cos| >= |sin| select, the ratio division),
  * rounds mult and ratio once to `dtype`, and uploads it to HBM (shared across
  * plans of the same dtype and kind).  Chooses the kernel configuration (tuned
- * record if one exists, else a fixed rule) and, for n beyond one workgroup's
- * LDS, a two-pass schedule with a plan-owned workspace.
+ * record if one exists, else a fixed rule; for few transforms, shapes with more
+ * and shorter workgroups, unless the caller tuned this size for as few) and,
+ * for n beyond one workgroup's LDS, a two-pass schedule with a plan-owned workspace.
  * Returns NULL on error (FFT_EINVAL for bad arguments, FFT_ENOMEM, FFT_EHIP).
  */
 fft_plan* fft_plan_create(int64_t n, int64_t batch, fft_dtype dtype, fft_table_kind kind);
@@ -255,7 +256,9 @@ int fft_table_build_radix4(int64_t n, fft_dtype dtype, fft_table_kind kind, int 
  * and records the fastest: later
  * fft_plan_create calls for this (n, dtype) in the process use it, and the
  * record is appended to the file named by the DSFFT_TUNE_FILE environment
- * variable (read back at the first plan creation of a process).  `report`
+ * variable (read back at the first plan creation of a process).  Plans of fewer
+ * than `batch` transforms may take the shapes for few transforms instead; a record
+ * in the file that no line "# batch B" precedes decides for every number.  `report`
  * receives a JSON array of the candidates' timings (up to `cap` bytes).
  */
 int fft_tune(int64_t n, int64_t batch, fft_dtype dtype, fft_table_kind kind, int reps,

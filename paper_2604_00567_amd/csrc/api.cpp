@@ -253,7 +253,10 @@ const FewCfg* few_half(int dtype, int mode, int log_nu, int64_t units, int cus) 
     return best;
 }
 
-static void few_transforms_choice(fft_plan* p) {
+// recorded: the schedule is one that the user's tuner found for so many transforms
+// or fewer; it stands, but for several whole transforms per workgroup.
+static void few_transforms_choice(fft_plan* p, bool recorded) {
+    if (recorded && (p->k2 || p->k1->upw == 1)) return;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess) return;
     if (p->k2) {
@@ -400,14 +403,17 @@ fft_plan* plan_create(int64_t n, int64_t batch, int dtype, int kind, const int* 
     }
     if (get_table(n, table_dtype(dtype), kind, inverse, &p->table, radix) != FFT_OK) return nullptr;
     int tuned[3];
-    if (!variants && radix == 2 && tuned_choice(dtype, p->log_n, tuned)) {
+    bool recorded = false;
+    int64_t tuned_batch = 0;
+    if (!variants && radix == 2 && tuned_choice(dtype, p->log_n, tuned, &tuned_batch)) {
         // a recorded tuning choice; fall back to the fixed rule if it no longer exists
-        if (choose_schedule(p.get(), tuned) != FFT_OK && choose_schedule(p.get(), nullptr) != FFT_OK)
-            return nullptr;
+        recorded = choose_schedule(p.get(), tuned) == FFT_OK;
+        if (!recorded && choose_schedule(p.get(), nullptr) != FFT_OK) return nullptr;
+        recorded = recorded && batch >= tuned_batch;
     } else if (choose_schedule(p.get(), variants) != FFT_OK) {
         return nullptr;
     }
-    if (!variants && radix == 2) few_transforms_choice(p.get());
+    if (!variants && radix == 2) few_transforms_choice(p.get(), recorded);
     size_workspace(p.get());
     if (p->ws_need && alloc_ws) {
         e = hipMalloc(&p->ws, p->ws_need);

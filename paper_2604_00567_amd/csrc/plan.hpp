@@ -60,7 +60,9 @@ fft_plan* plan_create(int64_t n, int64_t batch, int dtype, int kind, const int* 
                       bool inverse = false, int radix = 2, bool alloc_ws = true);
 // Largest workspace a two-pass plan asks for (its chunk cap).
 constexpr size_t kMaxWorkspaceBytes = (size_t)128 << 20;
-bool tuned_choice(int dtype, int log_n, int* variants);
+// The recorded choice, if any; *batch: plans of at least so many transforms take it
+// whatever the rule for few transforms says.
+bool tuned_choice(int dtype, int log_n, int* variants, int64_t* batch = nullptr);
 int plan_execute(fft_plan* p, const void* in, void* out, hipStream_t s);
 // Text of configuration k as plan p launches it (fft_plan_info, tuner report).
 std::string describe(const fft_plan* p, const KernelCfg* k);

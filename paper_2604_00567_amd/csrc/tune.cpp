@@ -6,7 +6,8 @@
 // in a process-wide registry that plan creation consults.  Records persist in
 // a plain-text file named by DSFFT_TUNE_FILE (one record per line:
 // "arch cus dtype log2n variant_a variant_b two_pass GB/s"; '#' starts a
-// comment line).  Records shipped
+// comment line, "# batch B" before a record says how many transforms it was
+// tuned with).  Records shipped
 // with the library (tuning_records.txt beside libdsfft.so, measured on the
 // target device) are read first; DSFFT_TUNE_FILE records override them.
 #include <dlfcn.h>
@@ -29,9 +30,15 @@
 
 namespace dsfft {
 
+constexpr int64_t kShipped = INT64_MAX;
+
 struct TuneRec {
     int va = 0, vb = 0, two = 0;
     double gbs = 0;
+    // How many transforms a plan needs for the record to decide its kernels where the
+    // rule for few transforms would choose others: those it was tuned with (1 if not
+    // known; kShipped for the library's own records, which always give way to the rule).
+    int64_t batch = 1;
 };
 
 static std::mutex g_tune_mu;
@@ -51,10 +58,11 @@ static std::string device_tag() {
 
 // One record per line; blank lines, lines starting with '#' and lines that do
 // not hold a well-formed record are skipped, so one bad line costs only itself.
-static void read_records(const std::string& path, const std::string& tag) {
+static void read_records(const std::string& path, const std::string& tag, bool shipped) {
     FILE* f = std::fopen(path.c_str(), "r");
     if (!f) return;
     char line[512];
+    long long batch = 1;                          // of a comment "# batch B" before a record
     while (std::fgets(line, sizeof line, f)) {
         const size_t len = std::strlen(line);
         if (len + 1 == sizeof line && line[len - 1] != '\n') {      // overlong: skip the rest
@@ -64,7 +72,10 @@ static void read_records(const std::string& path, const std::string& tag) {
             continue;
         }
         const char* q = line + std::strspn(line, " \t");
+        if (*q == '#') (void)std::sscanf(q, "# batch %lld", &batch);
         if (*q == '#' || *q == '\n' || *q == '\0') continue;
+        const int64_t tuned_batch = shipped ? kShipped : (batch > 0 ? batch : 1);
+        batch = 1;
         char arch[64];
         int cus, dt, m, va, vb, two;
         double gbs;
@@ -72,7 +83,7 @@ static void read_records(const std::string& path, const std::string& tag) {
         if (dt < DT_F16 || dt > DT_F16F32 || m < 1 || m > 20 || va < 0 || vb < 0 || (two != 0 && two != 1))
             continue;
         if (tag != std::string(arch) + " " + std::to_string(cus)) continue;
-        g_tuned[std::make_tuple(dt, m)] = TuneRec{va, vb, two, gbs};
+        g_tuned[std::make_tuple(dt, m)] = TuneRec{va, vb, two, gbs, tuned_batch};
     }
     std::fclose(f);
 }
@@ -91,12 +102,12 @@ static void load_records_locked() {
     g_tune_loaded = true;
     const std::string tag = device_tag();
     const std::string shipped = shipped_records();
-    if (!shipped.empty()) read_records(shipped, tag);
-    if (const char* path = std::getenv("DSFFT_TUNE_FILE")) read_records(path, tag);
+    if (!shipped.empty()) read_records(shipped, tag, true);
+    if (const char* path = std::getenv("DSFFT_TUNE_FILE")) read_records(path, tag, false);
 }
 
 // The tuned choice for (dtype, log2 n), if any: variants[3] = {a, b, two_pass}.
-bool tuned_choice(int dtype, int log_n, int* variants) {
+bool tuned_choice(int dtype, int log_n, int* variants, int64_t* batch) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     load_records_locked();
     auto it = g_tuned.find(std::make_tuple(dtype, log_n));
@@ -104,6 +115,7 @@ bool tuned_choice(int dtype, int log_n, int* variants) {
     variants[0] = it->second.va;
     variants[1] = it->second.vb;
     variants[2] = it->second.two;
+    if (batch) *batch = it->second.batch;
     return true;
 }
 
@@ -115,8 +127,8 @@ static void store_record(int dtype, int log_n, const TuneRec& r) {
     if (!path) return;
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%s %d %d %d %d %d %.1f\n", device_tag().c_str(), dtype, log_n, r.va, r.vb,
-                 r.two, r.gbs);
+    std::fprintf(f, "# batch %lld\n%s %d %d %d %d %d %.1f\n", (long long)r.batch, device_tag().c_str(), dtype,
+                 log_n, r.va, r.vb, r.two, r.gbs);
     std::fclose(f);
 }
 
@@ -231,7 +243,7 @@ int fft_tune(int64_t n, int64_t batch, fft_dtype dtype, fft_table_kind kind, int
             ++accepted;
             if (ms < best_ms) {
                 best_ms = ms;
-                best = TuneRec{v[0], v[1], v[2], gbs};
+                best = TuneRec{v[0], v[1], v[2], gbs, batch};
             }
         }
         delete p;
