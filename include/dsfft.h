@@ -286,11 +286,12 @@ int fft_config_count(int64_t n, fft_dtype dtype, int* single, int* cols, int* ro
  * transforms of 2^16 and 2^15 points (256 and 128 KiB, more than the batch
  * kernel's LDS) run whole in two list kernels of their own, one transform per
  * 1024-thread workgroup, over lists of their offsets.  In batches of more than
- * 2^25 elements the launches form one HIP graph built at the first execute and
- * replayed by every execute, whose list kernels run beside the first kernel
- * (branches with no dependency: the transforms are disjoint; up to 1.5
- * transforms of 2^16 points per compute unit, the two lists in one branch); new data
- * pointers are set on the graph's kernel nodes.  Smaller batches launch the
+ * 2^25 elements, and smaller ones whose 2^16-point transforms end in a short round
+ * of workgroups that others can fill, the launches form one HIP graph built at the
+ * first execute and replayed by every execute, whose list kernels run beside the
+ * first kernel (branches with no dependency: the transforms are disjoint; the two
+ * lists in one branch where that is faster); new data
+ * pointers are set on the graph's kernel nodes.  Other batches launch the
  * kernels in order on the caller's stream, and the column and row halves of
  * the transforms of a short list, with the intermediate in the output, unless
  * the call is in place.  (The kernels leave their work-queue counters at zero

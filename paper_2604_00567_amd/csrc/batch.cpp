@@ -57,7 +57,7 @@ struct fft_batch {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     int64_t phase0 = 0;                    // items of phase 0 (the rest are phase 1)
-    int grid = 0, grid0 = 0, grid1 = 0, resident = 1, cus = 1;
+    int grid = 0, grid0 = 0, grid1 = 0, resident = 1, cus = 1, route = 0;   // route: batch_route
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraphNode_t knode[2] = {nullptr, nullptr};
@@ -322,23 +322,60 @@ static hipKernelNodeParams list_params(const fft_batch* b, ListArgs& a, int list
     return kp;
 }
 
+// How a batch's launches are arranged, from the transforms nlist of its lists (2^16
+// points, 2^15), its elements and the device's compute units.
+//
+// In order, one kernel after the other on the caller's stream, up to kDirectElems
+// elements: a replay costs 20 us of launching with one node and 50 us and more with
+// a branch for each kernel (binary16, 2^6 .. 2^16 points, 20 transforms: 69 us by
+// graph, 21 in order; 300: 68 and 30; 2000, 25 M elements: 77 and 65).  A short list
+// (as for plans, split_limit) then runs split through the output unless the call
+// is in place.  But in order nothing runs beside the last round of the 2^16 list (one
+// workgroup per compute unit, 25 us), so where that round is short and there is
+// work to fill it, the batch replays a graph: 264 transforms of 2^16 points, 300 of 2^15 and
+// 2 M further elements 95 us in order, 78 in branches; 257, 128 and 8 M 97 and 80.
+//
+// A graph's list kernels and phase 0 are branches that fill each other's tails.  Its
+// third branch starts 36 us after the first, so the 2^15 list better follows the 2^16
+// one in one branch, if that has one round only, or if phase 0 has enough work to
+// fill the second: up to half a round of it (4096 transforms of 2^6 .. 2^16 points, branch
+// for each / lists in one, in us: 379 of 2^16 points 116.9 / 109.9, 405 123.4 / 127.7), from
+// 7 M elements on (300 of 2^16, 256 of 2^15: with 2 M 80 / 86, with 8 M 97 / 88), or 12 M
+// where the 2^15 list ends in a short round as well (380, 300, 8 M: 105 / 120; 300, 257,
+// 16 M: 114 / 109).
+//
+// Over 1350 batches of 0 to 600 and 0 to 900 transforms of the lists and up to 16 M
+// further elements none is slower than one graph with a branch for each kernel was
+// with kernels that loaded every twiddle; in order up to 2^25 elements and lists in one up to
+// 1.5 transforms of 2^16 per compute unit alone were, in 119 of them, by up to 16 %.
+constexpr int64_t kDirectElems = int64_t(1) << 25;
+enum { ROUTE_IN_ORDER = 0, ROUTE_LISTS_IN_ONE = 1, ROUTE_BRANCHES = 2 };
+
+// Whether `count` workgroups, one per compute unit at a time, end in a round that
+// takes at most `eighths` eighths of the compute units.
+static bool short_last_round(int64_t count, int cus, int eighths) {
+    return count > cus && count % cus != 0 && 8 * (count % cus) <= (int64_t)eighths * cus;
+}
+
+int batch_route(const int64_t* nlist, int64_t total, int cus) {
+    const int64_t n16 = nlist[0], n15 = nlist[1];
+    const int64_t rest = total - (n16 << kListLog[0]) - (n15 << kListLog[1]);
+    const int64_t beside = rest + (n15 << kListLog[1]);
+    if (total <= kDirectElems && !(short_last_round(n16, cus, 3) && beside >= int64_t(2) << 20)) return ROUTE_IN_ORDER;
+    if (n16 <= cus) return ROUTE_LISTS_IN_ONE;
+    const int64_t fill = int64_t(short_last_round(n15, cus, 2) ? 12 : 7) << 20;
+    return 2 * n16 <= 3 * (int64_t)cus && rest >= fill ? ROUTE_LISTS_IN_ONE : ROUTE_BRANCHES;
+}
+
 // Builds the graph once: the list kernels (those with transforms) and phase 0 as
-// independent branches (they touch disjoint transforms, so each can fill the
-// others' tails), then phase 1 after phase 0 (each phase a persistent kernel
-// whose workgroups only claim items from a queue, so sharing the device with
-// the list kernels never blocks them).  A replay starts its branches one after the
-// other, the third 36 us after the first; so the 2^15 list follows the 2^16 one in
-// one branch, where the second round of 2^16 workgroups (one per compute unit) still
-// finds room: two branches share the compute units that the first round frees
-// equally, and phase 0's workgroups stay until its queue is empty.  Up to half a
-// round it does: 4096 transforms of 2^6 .. 2^16 points, 256 compute units, branch for
-// each / lists in one, in us: 370 of 2^16 points 120.4 / 111.0, 379 116.9 / 109.9, 393
-// 120.5 / 126.5, 405 123.4 / 127.7; other batches with 177 258.2 / 250.4, 296 100.0
-// / 98.8, 440 135.6 / 147.4, 587 158.5 / 175.0.
+// independent branches, or the lists in one (they touch disjoint transforms, so each
+// can fill the others' tails), then phase 1 after phase 0 (each phase a persistent
+// kernel whose workgroups only claim items from a queue, so sharing the device with
+// the list kernels never blocks them).
 static int build_graph(fft_batch* b, const void* in, void* out) {
     hipError_t e;
     if ((e = hipGraphCreate(&b->graph, 0)) != hipSuccess) return hip_error(e, "hipGraphCreate");
-    const bool lists_in_one = 2 * b->nlist[0] <= 3 * (int64_t)b->cus;
+    const bool lists_in_one = b->route == ROUTE_LISTS_IN_ONE;
     hipGraphNode_t prev = nullptr;
     for (int i = 0; i < kNumLists; ++i) {
         if (b->nlist[i] == 0) continue;
@@ -387,14 +424,7 @@ static int retarget(fft_batch* b, const void* in, void* out) {
     return FFT_OK;
 }
 
-// Batches of up to kDirectElems elements launch their kernels one after the other
-// on the caller's stream; larger ones replay a graph whose list kernels and phase
-// 0 fill each other's tails.  A replay costs 20 us of launching with one node and
-// 50 us and more with a branch for each kernel: binary16, 2^6 .. 2^16 points, 20
-// transforms 69 us by graph and 21 in order, 300 68 and 30, 2000 (25 M
-// elements) 77 and 65, 4096 (48 M) 118 and 127 (110 with the lists in one branch).  In order, a short list (as for
-// plans, split_limit) runs split through the output unless the call is in place.
-constexpr int64_t kDirectElems = int64_t(1) << 25;
+// The launches of ROUTE_IN_ORDER.
 static int launch_direct(fft_batch* b, const void* in, void* out, hipStream_t s) {
     hipError_t e = hipSuccess;
     const void* lt = b->table->ptr;
@@ -435,7 +465,7 @@ int batch_execute(fft_batch* b, const void* in, void* out, hipStream_t s) {
     // and a replay the graph whose nodes the call has just pointed at its buffers.
     std::lock_guard<std::mutex> lock(b->launch_mu);
     int rc = FFT_OK;
-    if (b->total <= kDirectElems) return launch_direct(b, in, out, s);
+    if (b->route == ROUTE_IN_ORDER) return launch_direct(b, in, out, s);
     if (!b->exec) rc = build_graph(b, in, out);
     else if (b->cap_in != in || b->cap_out != out) rc = retarget(b, in, out);
     if (rc != FFT_OK) return rc;
@@ -491,6 +521,7 @@ fft_batch* batch_create(const int64_t* n, int64_t count, int dtype, int kind, co
     }
     if (get_table(nmax, dtype, kind, false, &b->table) != FFT_OK) return nullptr;
     if (build_items(b.get()) != FFT_OK) return nullptr;
+    b->route = batch_route(b->nlist, b->total, b->cus);
     if (upload(b.get()) != FFT_OK) return nullptr;
     return b.release();
 }
