@@ -170,7 +170,8 @@ int fft_table_build_dir(int64_t n, fft_dtype dtype, fft_table_kind kind, int dir
  * ",enc=select" / ",enc=branch" for the path-encoding variants, ",quarter"
  * where the kernel that runs loads half of each stage's twiddles (B is that
  * kernel's), "; out of place: split through the output, ..." where calls that
- * are not in place run as column and row kernels, and for a
+ * are not in place run as column and row kernels, "; in place: U columns and rows
+ * per workgroup" where a two-pass plan's calls in place take others, and for a
  * two-pass plan " | rows:... | chunk=C" (its second kernel, and the
  * transforms per workspace chunk).  P says where
  * twiddles come from besides per-lane table loads: 1 persistent workgroups

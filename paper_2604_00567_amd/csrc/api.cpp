@@ -207,6 +207,42 @@ static const KernelCfg* narrow_kernel(const fft_plan* p, const KernelCfg* tuned,
     }
 }
 
+// The configuration of (dtype, mode, log_nu) with `upw` units per workgroup, its
+// quarter form compiled where one has it; null if there is none.
+static const KernelCfg* kernel_of_width(int dtype, int mode, int log_nu, int upw) {
+    const KernelCfg* best = nullptr;
+    for (int v = 0;; ++v) {
+        const KernelCfg* k = find_kernel(dtype, mode, log_nu, v);
+        if (!k) return best;
+        if (k->staged || k->encoding || k->upw != upw) continue;
+        if (!best || (k->launch_quarter && !best->launch_quarter)) best = k;
+    }
+}
+
+// The kernels of calls in place of a two-pass plan of few transforms.  What a call reads
+// was then mostly written by the call before it (or by the caller's kernels), and a line
+// that one XCD's rows write while others have read it costs more than the narrow
+// launches gain; so columns and rows have one width, with runs of 64 bytes of the
+// stored data where both launches are at most one workgroup per compute unit, else of
+// 128 or 256 where the columns are, and the rows at most two.  In place, narrow_kernel's pair
+// / this one / the tuned pair, in us: binary16 2^17 x 4 11.2 / 9.0 / 10.6, x 12 15.5 / 12.1
+// / 12.8, x 24 22.3 / 16.1 / 17.2; binary32 2^17 x 12 22.5 / 17.7 / 18.3; binary16 storage
+// 2^16 x 24 18.0 / 15.5 / 16.5.  Pairs of one width stay (binary32 2^18 x 2 11.5, tuned 15.9).
+static void in_place_choice(fft_plan* p, int cus) {
+    if (p->k1->upw == p->k2->upw && p->k1->upw * work_elem_bytes(p->dtype) >= 64) return;
+    const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
+    for (int run = 64; run <= 256; run *= 2) {
+        const int upw = run / elem_bytes(p->dtype);
+        if ((p->batch << m2) > (int64_t)upw * cus || (p->batch << m1) > (int64_t)upw * cus * (run > 64 ? 2 : 1)) continue;
+        const KernelCfg* c = kernel_of_width(p->dtype, MODE_COLS, m1, upw);
+        const KernelCfg* r = kernel_of_width(p->dtype, MODE_ROWS, m2, upw);
+        if (!c || !r) continue;
+        p->in_place_k1 = c;
+        p->in_place_k2 = r;
+        return;
+    }
+}
+
 // Whole transforms: the configuration with one transform per workgroup on
 // the most lanes (binary32 N = 1024 x 16: 4.4 against 5.6 us per kernel; 2^14 x
 // 256 18.5 against 21.1 us; binary16 2^15 x 96 13.1 against 16.2 us).
@@ -263,6 +299,7 @@ static void few_transforms_choice(fft_plan* p, bool recorded) {
         const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
         p->k1 = p->k1_plain = narrow_kernel(p, p->k1, p->batch << m2, cus);
         p->k2 = narrow_kernel(p, p->k2, p->batch << m1, cus);
+        in_place_choice(p, cus);
         return;
     }
     if (p->batch * 16 <= (int64_t)split_limit(p->dtype, p->log_n) * cus) {
@@ -348,7 +385,9 @@ int launch_plan_ws(const fft_plan* p, const void* in, void* out, hipStream_t s, 
         if (e != hipSuccess) return hip_error(e, "launch");
         return FFT_OK;
     }
-    const LaunchFn cols = plan_launch(p, p->k1), rows = plan_launch(p, p->k2);
+    const bool in_place = in == out && p->in_place_k1;
+    const LaunchFn cols = plan_launch(p, in_place ? p->in_place_k1 : p->k1);
+    const LaunchFn rows = plan_launch(p, in_place ? p->in_place_k2 : p->k2);
     const int m1 = p->k1->log_nu, m2 = p->k2->log_nu;
     const size_t eb = (size_t)elem_bytes(p->dtype);
     for (int64_t b0 = 0; b0 < p->batch; b0 += chunk) {
@@ -527,6 +566,8 @@ int fft_plan_info(const fft_plan* p, int64_t* n, int64_t* batch, int* dtype, int
         if (p->few_cols)
             d += "; out of place: split through the output, " + std::to_string(p->few_cols->upw) + " columns and " +
                  std::to_string(p->few_rows->upw) + " rows per workgroup";
+        if (p->in_place_k1)
+            d += "; in place: " + std::to_string(p->in_place_k1->upw) + " columns and rows per workgroup";
         if (p->k2) d += " | " + describe(p, p->k2) + " | chunk=" + std::to_string(p->chunk);
         std::snprintf(config_out, cap, "%s", d.c_str());
     }

@@ -1655,10 +1655,19 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
 // XCD takes runs of kColumnRun consecutive blocks, so that the runs that
 // share a line or a DRAM page are in one L2 at one time.  Runs of 8 to 64 measure
 // alike; any remainder past whole groups of 8 runs keeps its order.
+// Blocks of whole lines (LINES) share none, and launches of up to kPlainOrderBytes
+// stay in the L2s: those keep the plain order, where in calls in place the XCD that
+// reads a line is mostly the one whose row workgroup wrote it last (in place,
+// binary16 2^17 x 32 with 32 columns a block 26.1 us ordered, 18.9 plain; binary32
+// 2^18 x 8 23.2 and 20.0; out of place the same within 1 %).  Above, ordered ones are
+// faster (binary16 2^18 x 36 in place 32.3 us, plain 34.9; 128 MiB of binary16 2^17
+// columns 48.7 and 55.8).
 constexpr int kColumnRun = 32;
-__device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk) {
+constexpr int64_t kPlainOrderBytes = int64_t(16) << 20;
+template <bool LINES>
+__device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk, int64_t bytes) {
     constexpr int64_t group = 8 * kColumnRun;
-    if (b >= nblk / group * group) return b;
+    if (b >= nblk / group * group || (LINES && bytes <= kPlainOrderBytes)) return b;
     return b / group * group + b % 8 * kColumnRun + b % group / 8;
 }
 
@@ -1808,7 +1817,9 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
         // PIPE = 5: the middle pass from LDS (as PIPE = 3) and the last pass's
         // twiddles prefetched a pass ahead (as PIPE = 2)
         constexpr int TWL = (PIPE == 3 || PIPE == 4 || PIPE == 5) ? PIPE : 0;
-        const int64_t blk = MODE == MODE_COLS ? column_block(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+        int64_t blk = blockIdx.x;
+        if constexpr (MODE == MODE_COLS)
+            blk = column_block<UPW * (int)sizeof(SI) >= 128>(blk, gridDim.x, (units << LOG_NU) * (int64_t)sizeof(SI));
         const GridGeoT<PIPE == 2 || PIPE == 5, ENC, TWL> gp{blk * UPW, units, log_m, (int)threadIdx.x};
         unit_pass<E, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, 0, 0>(v, lds, lt, in, out,
                                                                                gp);

@@ -42,6 +42,9 @@ struct fft_plan {
     const dsfft::KernelCfg* k1 = nullptr;   // single kernel, or the column kernel
     const dsfft::KernelCfg* k1_plain = nullptr;  // k1's size without 16-byte staging
     const dsfft::KernelCfg* k2 = nullptr;   // row kernel of the two-pass schedule
+    // the two kernels of calls in place of few transforms (null: k1 and k2)
+    const dsfft::KernelCfg* in_place_k1 = nullptr;
+    const dsfft::KernelCfg* in_place_k2 = nullptr;
     // calls of few whole transforms that are not in place: the two halves of
     // the schedule through the output (null: k1 serves every call)
     const dsfft::FewCfg* few_cols = nullptr;
