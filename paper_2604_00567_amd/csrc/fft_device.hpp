@@ -1665,7 +1665,7 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
 constexpr int kColumnRun = 32;
 constexpr int64_t kPlainOrderBytes = int64_t(16) << 20;
 template <bool LINES>
-__device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk, int64_t bytes) {
+__host__ __device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk, int64_t bytes) {
     constexpr int64_t group = 8 * kColumnRun;
     if (b >= nblk / group * group || (LINES && bytes <= kPlainOrderBytes)) return b;
     return b / group * group + b % 8 * kColumnRun + b % group / 8;
