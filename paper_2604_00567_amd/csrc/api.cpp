@@ -188,9 +188,12 @@ static int small_limit(int dtype) {
 
 // The narrowest configuration of (dtype, mode, log_nu), fewest units per
 // workgroup, whose launch over `units` still has at most one workgroup per
-// compute unit; `tuned` if none has.  (More workgroups than that queue behind each
-// other, and the wider shapes use the memory lines better: binary16 2^18 x 1
-// 12.0 -> 7.5 us, x 8 15.8 -> 14.1; binary32 2^18 x 4 18.0 -> 13.1 us.)  A row kernel
+// compute unit; `tuned` if none has (binary16 2^18 x 1 12.0 -> 7.5 us, x 8 15.8 ->
+// 14.1; binary32 2^18 x 4 18.0 -> 13.1 us).  Past that the wider shapes use the memory
+// lines better in binary16 (2^18 x 7 in columns and rows of 16: 13.0 us, no pair
+// of the compiled ones faster).  Two to four of the eight-unit workgroups fit a compute unit, and
+// where their runs are 64 bytes two rounds of them can be faster still (binary32
+// 2^18 x 7 17.3 us in eights, 20.5 here; 2^20 x 4 the same): not done.  A row kernel
 // may also be wider than the tuned one where that brings the launch down to
 // one round and two workgroups still share a compute unit (binary16 2^17 x 32 19.3
 // -> 17.2 us; with one per compute unit, binary16 2^18 x 32, 25.0 -> 27.3).
@@ -265,7 +268,10 @@ static const KernelCfg* widest_kernel(const fft_plan* p) {
 // and past the limits: binary16 2^14 x 48 7.6 / 7.8, x 64 8.5 / 7.9; 2^15 x 64
 // 11.8 / 12.8, x 96 15.6 / 13.1; 2^16 x 1 6.2 / 24.5, x 96 22.8 / 25.8, x 128
 // 28.3 / 27.2; binary32 2^13 x 48 8.3 / 8.5; 2^14 x 64 12.0 / 12.6; 2^15 x 96
-// 22.6 / 25.9.
+// 22.6 / 25.9.  (Calls from C, one after the other; 2^14 x 1 5.3 / 7.1, binary32 2^13 x 1
+// 5.6 / 7.7.  Through Python the two launches take 7.9 to 8.3 us themselves: the 64 KiB
+// transforms gain only in calls that are waited for, 18.5 / 19.5 and 18.1 / 20.1 us, and
+// lose up to 1 us in binary16 when called one after the other, 8.0 / 7.1.)
 int split_limit(int dtype, int log_n) {
     if (dtype == DT_F16F32) return 0;      // its intermediate does not fit in its output
     const int log_bytes = log_n + (dtype == DT_F16 ? 2 : 3);

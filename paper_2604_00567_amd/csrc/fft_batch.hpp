@@ -237,9 +237,14 @@ fft_batch_kernel(const E* in, E* out, E* ws, const typename TwOf<E>::type* __res
     copy_table_prefix<typename TwOf<E>::type, batch_twiddle_prefix<E>(), kBatchThreads>(lt, lds_raw);
     E* lds = reinterpret_cast<E*>(lds_raw + batch_prefix_bytes<E>());
     // A workgroup's first item is its own index (the grid is at most nitems), so
-    // that its data loads wait for no claim.  Claims run one item ahead: the
-    // claim of the next item is issued when the current one starts, so its round trip overlaps the current item's
-    // work, and published in LDS when the item ends.  Two slots alternate:
+    // that its data loads wait for no claim: 3 to 6 us of a batch in order (8 M
+    // elements 43.8 -> 38.0, 28 M 69.2 -> 66.4).  In a graph the first items, the largest,
+    // then wait for their own workgroups beside the list kernels, where any resident
+    // workgroup could have claimed them: 16 batches above 2^25 elements took from 3 %
+    // less (45 M 106.4 -> 103.5) to 2 % more (50 M 111.7 -> 113.4).
+    // Claims run one item ahead: the claim of the next item is issued when the
+    // current one starts, so its round trip overlaps the current item's work, and
+    // published in LDS when the item ends.  Two slots alternate:
     // the slot written at the end of item k was last read after the barrier
     // that ended item k - 2, and every thread has since passed the barrier
     // that ended item k - 1.

@@ -139,8 +139,8 @@ int fft_serve_slot_launch(fft_serve_slot* s, const int64_t* n, const int64_t* ba
         return hip_error(e, "launch(work list copy)");
     const int64_t* d_lists = (const int64_t*)(s->d_stage + ib + ob);
     for (int i = 0; i < kNumLists; ++i) {
-        if (s->nlist[i] && (e = launch_batch_list(i, s->table->quarter, data, data, s->table->ptr, d_lists, s->nlist[i], st)) !=
-                               hipSuccess)
+        if (s->nlist[i] && (e = launch_batch_list(i, s->table->quarter, data, data, s->table->ptr, d_lists, s->nlist[i],
+                                                  st)) != hipSuccess)
             return hip_error(e, "launch(list)");
         d_lists += s->nlist[i];
     }
