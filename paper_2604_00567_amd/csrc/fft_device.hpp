@@ -830,10 +830,16 @@ constexpr int lds_twiddle_last_pass() {
 // q + L0 c at q + L0 quarter_slot(c) of the pass's part of the copy, which
 // follows the parts of the passes before it.  Binary32 2^13 then takes 38.9 KiB
 // of LDS instead of 42.5, four workgroups per CU instead of three: 256 MiB
-// batches 5243 -> 5695 GB/s.  PIPE = 4 keeps the whole run: its copy serves
-// short workgroups of 2^7 to 2^10 points, which measured faster with the
-// plain copy (binary16 2^9 6489 against 6197 GB/s, 2^10 6198 against 6040).
-constexpr bool compact_copy(int enc, int pipe) { return is_quarter(enc) && pipe != 4; }
+// batches 5243 -> 5695 GB/s; binary32 2^12 gains 2 % without one more (x 732
+// 10.1 -> 9.3 us).  Whole transforms of up to 2^11 points keep the whole run:
+// binary32 2^11 x 1953 10.9 us against 11.7 with the compact copy, 2^10 x 4096
+// 10.8 against 11.5 (11.0 against 12.4 over three pairs of buffers), binary16
+// 2^11 1 % faster, mixed 2^10 0.6 % slower, the others of that size equal.  So
+// does PIPE = 4, short workgroups of 2^7 to 2^10 points (binary16 2^9 6489
+// against 6197 GB/s, 2^10 6198 against 6040).
+constexpr bool compact_copy(int enc, int pipe, int mode, int log_nu) {
+    return is_quarter(enc) && pipe != 4 && !(mode == MODE_SMALL && log_nu <= 11);
+}
 constexpr int quarter_slot(int c) {
     if (c < 2) return 0;
     int top = 1;
@@ -850,7 +856,7 @@ template <int LOG_NU, int LOG_E, int MODE, int LANE, class PP, int PIPE, int ENC
 constexpr int lds_twiddle_entries() {
     constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PP, PIPE>();
     if (LAST == 0) return 0;
-    if (compact_copy(ENC, PIPE)) return quarter_copy_offset<PP>(LAST + 1);
+    if (compact_copy(ENC, PIPE, MODE, LOG_NU)) return quarter_copy_offset<PP>(LAST + 1);
     return (1 << (PP::log_l0(LAST) + PP::lr(LAST))) - (1 << PP::log_l0(1));
 }
 // Row units (PIPE = 3): the first pass of row q0 takes entries
@@ -1406,7 +1412,7 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                 const TW* ltw = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) +
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
                 const int q = (g + G * u) >> LOGM;
-                if constexpr (compact_copy(PENC, Geo::kTwiddleLds)) {
+                if constexpr (compact_copy(PENC, Geo::kTwiddleLds, MODE, LOG_NU)) {
                     ltw += quarter_copy_offset<PP>(P);
 #pragma unroll
                     for (int c = 1; c < R; ++c)
@@ -1792,7 +1798,7 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
             static_assert(TE > 0 && (TE * sizeof(TW)) % 16 == 0 && ((1 << LR0) * sizeof(TW)) % 16 == 0,
                           "LDS twiddles: whole 16-byte chunks from a 16-byte aligned start");
             uint4* dst = reinterpret_cast<uint4*>(lds_raw + lds_twiddle_offset<E, LOG_E, MODE, UPW, PPT>());
-            if constexpr (compact_copy(ENC, PIPE)) {
+            if constexpr (compact_copy(ENC, PIPE, MODE, LOG_NU)) {
                 // pass by pass: entry k of its part is table entry k + L0 for
                 // k < L0 and k + L0 2^floor(log2(k / L0)) beyond
                 constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE>();
