@@ -328,7 +328,8 @@ int fft_batch_tune(fft_dtype dtype, fft_table_kind kind, int reps, int* choice_1
                    int* choice_4096);
 
 /* Enqueues the whole uneven batch on `stream` (device pointers, packed
- * layout, element-aligned; in == out allowed).  Async. */
+ * layout, element-aligned; in == out allowed).  Async.  In a stream capture its
+ * kernels are captured one by one. */
 int fft_batch_execute(fft_batch* batch, const void* in, void* out, void* stream);
 
 /* Total elements of the packed layout. */

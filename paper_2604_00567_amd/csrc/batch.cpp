@@ -465,7 +465,11 @@ int batch_execute(fft_batch* b, const void* in, void* out, hipStream_t s) {
     // and a replay the graph whose nodes the call has just pointed at its buffers.
     std::lock_guard<std::mutex> lock(b->launch_mu);
     int rc = FFT_OK;
-    if (b->route == ROUTE_IN_ORDER) return launch_direct(b, in, out, s);
+    // A replay launched into a stream capture leaves no node in it (it runs at once or
+    // not at all); in order the kernels are captured one by one.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (b->route != ROUTE_IN_ORDER && s) (void)hipStreamIsCapturing(s, &capture);
+    if (b->route == ROUTE_IN_ORDER || capture == hipStreamCaptureStatusActive) return launch_direct(b, in, out, s);
     if (!b->exec) rc = build_graph(b, in, out);
     else if (b->cap_in != in || b->cap_out != out) rc = retarget(b, in, out);
     if (rc != FFT_OK) return rc;
