@@ -834,11 +834,12 @@ constexpr int lds_twiddle_last_pass() {
 // 10.1 -> 9.3 us).  Whole transforms of up to 2^11 points keep the whole run:
 // binary32 2^11 x 1953 10.9 us against 11.7 with the compact copy, 2^10 x 4096
 // 10.8 against 11.5 (11.0 against 12.4 over three pairs of buffers), binary16
-// 2^11 1 % faster, mixed 2^10 0.6 % slower, the others of that size equal.  So
-// does PIPE = 4, short workgroups of 2^7 to 2^10 points (binary16 2^9 6489
-// against 6197 GB/s, 2^10 6198 against 6040).
-constexpr bool compact_copy(int enc, int pipe, int mode, int log_nu) {
-    return is_quarter(enc) && pipe != 4 && !(mode == MODE_SMALL && log_nu <= 11);
+// 2^11 1 % faster, the others of that size equal, but not with data stored in
+// binary16 and computed in binary32 (MIXED: 2^10 x 65536 107.7 us compact,
+// 108.9 plain).  PIPE = 4, short workgroups of 2^7 to 2^10 points, keeps it always
+// (binary16 2^9 6489 against 6197 GB/s, 2^10 6198 against 6040).
+constexpr bool compact_copy(int enc, int pipe, int mode, int log_nu, bool mixed) {
+    return is_quarter(enc) && pipe != 4 && (mixed || !(mode == MODE_SMALL && log_nu <= 11));
 }
 constexpr int quarter_slot(int c) {
     if (c < 2) return 0;
@@ -852,11 +853,11 @@ constexpr int quarter_copy_offset(int pass) {
     for (int p = 1; p < pass; ++p) n += 1 << (PP::log_l0(p) + PP::lr(p) - 1);
     return n;
 }
-template <int LOG_NU, int LOG_E, int MODE, int LANE, class PP, int PIPE, int ENC = ENC_TABLE>
+template <int LOG_NU, int LOG_E, int MODE, int LANE, class PP, int PIPE, int ENC = ENC_TABLE, bool MIXED = false>
 constexpr int lds_twiddle_entries() {
     constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PP, PIPE>();
     if (LAST == 0) return 0;
-    if (compact_copy(ENC, PIPE, MODE, LOG_NU)) return quarter_copy_offset<PP>(LAST + 1);
+    if (compact_copy(ENC, PIPE, MODE, LOG_NU, MIXED)) return quarter_copy_offset<PP>(LAST + 1);
     return (1 << (PP::log_l0(LAST) + PP::lr(LAST))) - (1 << PP::log_l0(1));
 }
 // Row units (PIPE = 3): the first pass of row q0 takes entries
@@ -874,9 +875,11 @@ constexpr size_t lds_twiddle_offset() {
     return (unit_lds_elems<E, LOG_E, MODE, UPW, PP>() * sizeof(E) + 15) / 16 * 16;
 }
 // LDS bytes of a workgroup: the exchange area, and with PIPE = 3, 4 or 5 the twiddle copy.
-template <class E, int LOG_NU, int LOG_E, int MODE, int UPW, int LANE, int PIPE, class PP, int ENC = ENC_TABLE>
+// S: the stored element.
+template <class E, int LOG_NU, int LOG_E, int MODE, int UPW, int LANE, int PIPE, class PP, int ENC = ENC_TABLE,
+          class S = E>
 constexpr size_t unit_lds_bytes() {
-    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PP, PIPE, ENC>() +
+    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PP, PIPE, ENC, sizeof(S) != sizeof(E)>() +
                        lds_row_twiddle_entries<MODE, UPW, PP, PIPE, ENC>();
     if (TE == 0) return unit_lds_elems<E, LOG_E, MODE, UPW, PP>() * sizeof(E);
     return lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>() + (size_t)TE * sizeof(TwT<E, ENC>);
@@ -884,12 +887,13 @@ constexpr size_t unit_lds_bytes() {
 // Whether a configuration fits a workgroup's LDS for element type E (the
 // configuration list serves both element sizes; entries that do not fit are
 // neither compiled nor offered).  PIPE = 3, 4 and 5 also need a pass to serve.
-template <class E, int LOG_NU, int LOG_E, int MODE, int UPW, int LANE, int PIPE, class PP, int ENC = ENC_TABLE>
+template <class E, int LOG_NU, int LOG_E, int MODE, int UPW, int LANE, int PIPE, class PP, int ENC = ENC_TABLE,
+          class S = E>
 constexpr bool unit_fits() {
     if ((PIPE == 3 || PIPE == 4 || PIPE == 5) && lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PP, PIPE>() == 0 &&
         lds_row_twiddle_entries<MODE, UPW, PP, PIPE>() == 0)
         return false;
-    return unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PP, ENC>() <= kLdsBytes;
+    return unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PP, ENC, S>() <= kLdsBytes;
 }
 
 // ------------------------------------------------------------------ the kernel
@@ -1412,7 +1416,7 @@ __device__ __forceinline__ void unit_pass(E* v, E* lds, const TwT<E, Geo::kEncod
                 const TW* ltw = reinterpret_cast<const TW*>(reinterpret_cast<const unsigned char*>(lds) +
                                                             lds_twiddle_offset<E, LOG_E, MODE, UPW, PP>());
                 const int q = (g + G * u) >> LOGM;
-                if constexpr (compact_copy(PENC, Geo::kTwiddleLds, MODE, LOG_NU)) {
+                if constexpr (compact_copy(PENC, Geo::kTwiddleLds, MODE, LOG_NU, sizeof(SI) != sizeof(E))) {
                     ltw += quarter_copy_offset<PP>(P);
 #pragma unroll
                     for (int c = 1; c < R; ++c)
@@ -1684,7 +1688,7 @@ __host__ __device__ __forceinline__ int64_t column_block(int64_t b, int64_t nblk
 template <class E, class S, int LOG_NU, int LOG_E, int UPW, int MODE, int LANE, int PIPE, int ENC, class PP>
 constexpr int mixed_waves() {
     if (std::is_same_v<E, S> || MODE != MODE_SMALL || LOG_E != 5) return 1;
-    constexpr size_t lds = unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PP, ENC>();
+    constexpr size_t lds = unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PP, ENC, S>();
     return (int)(kLdsBytes / lds) * (UPW << (LOG_NU - LOG_E)) >= 4 * 4 * 64 ? 4 : 1;
 }
 
@@ -1792,13 +1796,14 @@ __device__ __forceinline__ void unit_kernel_body(const SI* in, SO* out, const Tw
             // pass 1 reads it
             using PPT = PassPlan<LOG_NU, LR0, LR1, LR2, LANE>;
             using TW = TwT<E, ENC>;
-            constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE, ENC>();
+            constexpr bool MIXED = sizeof(SI) != sizeof(E);
+            constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE, ENC, MIXED>();
             constexpr int CHUNKS = (int)(TE * sizeof(TW) / 16);
             constexpr int NT = (UPW / UPL) << (LOG_NU - LOG_E);
             static_assert(TE > 0 && (TE * sizeof(TW)) % 16 == 0 && ((1 << LR0) * sizeof(TW)) % 16 == 0,
                           "LDS twiddles: whole 16-byte chunks from a 16-byte aligned start");
             uint4* dst = reinterpret_cast<uint4*>(lds_raw + lds_twiddle_offset<E, LOG_E, MODE, UPW, PPT>());
-            if constexpr (compact_copy(ENC, PIPE, MODE, LOG_NU)) {
+            if constexpr (compact_copy(ENC, PIPE, MODE, LOG_NU, MIXED)) {
                 // pass by pass: entry k of its part is table entry k + L0 for
                 // k < L0 and k + L0 2^floor(log2(k / L0)) beyond
                 constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, LANE, PPT, PIPE>();

@@ -52,7 +52,7 @@ static constexpr bool cfg_fits() {
     // staged blocks pass through the whole exchange area, which a two-round
     // exchange halves
     if (STG && exchange_rounds<E, LOG_E, MODE, UPW, PassPlan<LOG_NU, LR0, LR1, LR2, LANE>>() == 2) return false;
-    return unit_fits<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC>();
+    return unit_fits<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC, S>();
 }
 
 // The kernel of a configuration: the pipelined entry (with its occupancy
@@ -91,7 +91,7 @@ static hipError_t launch_unit(const void* in, void* out, const void* lt, int64_t
     } else {
         constexpr int NT = (UPW / UPL) << (LOG_NU - LOG_E);
         constexpr size_t LDS =
-            unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC>();
+            unit_lds_bytes<E, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE, PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC, S>();
         auto kern = kernel_ptr<E, S, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC>();
         int64_t grid = (units + UPW - 1) / UPW;
         if (grid <= 0) return hipSuccess;
@@ -156,7 +156,7 @@ static constexpr LaunchFn launch_quarter() {
      launch_quarter<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC, \
                     ENC_QUARTER_INV>(),                                                               \
      unit_lds_bytes<ELEM_T, LOG_NU, LOG_E, MODE, UPW, LANE, PIPE,                               \
-                    PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC_QUARTER>(),                     \
+                    PassPlan<LOG_NU, LR0, LR1, LR2, LANE>, ENC_QUARTER, STORE_T>(),            \
      kernel_entry<ELEM_T, STORE_T, LOG_NU, LOG_E, UPW, UPL, MODE, LR0, LR1, LR2, STG, LANE, PIPE, ENC>()},
 #define CFGU(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL)                   \
     CFGE(MODE, LOG_NU, LOG_E, UPW, LR0, LR1, LR2, STG, LANE, PIPE, UPL, ENC_TABLE)

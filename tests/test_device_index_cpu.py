@@ -63,7 +63,7 @@ template <int LOG_L0, int LR> static void slots() {
 }
 
 // The parts of a compact copy follow each other and fill it.
-template <int LOG_NU, int LOG_E, int MODE, int PIPE, int LR0, int LR1, int LR2> static void copy() {
+template <int LOG_NU, int LOG_E, int MODE, int PIPE, int LR0, int LR1, int LR2, bool MIXED = false> static void copy() {
     using PP = PassPlan<LOG_NU, LR0, LR1, LR2, 0>;
     constexpr int LAST = lds_twiddle_last_pass<LOG_NU, LOG_E, MODE, 0, PP, PIPE>();
     EXPECT(LAST >= 1);
@@ -72,10 +72,10 @@ template <int LOG_NU, int LOG_E, int MODE, int PIPE, int LR0, int LR1, int LR2> 
         EXPECT(quarter_copy_offset<PP>(p) == at);
         at += (1 << (PP::log_l0(p) + PP::lr(p))) / 2;
     }
-    constexpr bool COMPACT = compact_copy(ENC_QUARTER, PIPE, MODE, LOG_NU);
-    EXPECT(!compact_copy(ENC_TABLE, PIPE, MODE, LOG_NU));
-    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, 0, PP, PIPE, ENC_QUARTER>();
-    constexpr int PLAIN = lds_twiddle_entries<LOG_NU, LOG_E, MODE, 0, PP, PIPE, ENC_TABLE>();
+    constexpr bool COMPACT = compact_copy(ENC_QUARTER, PIPE, MODE, LOG_NU, MIXED);
+    EXPECT(!compact_copy(ENC_TABLE, PIPE, MODE, LOG_NU, MIXED));
+    constexpr int TE = lds_twiddle_entries<LOG_NU, LOG_E, MODE, 0, PP, PIPE, ENC_QUARTER, MIXED>();
+    constexpr int PLAIN = lds_twiddle_entries<LOG_NU, LOG_E, MODE, 0, PP, PIPE, ENC_TABLE, MIXED>();
     EXPECT(TE % 2 == 0 && (COMPACT ? TE == at && TE <= PLAIN : TE == PLAIN));
 }
 
@@ -105,7 +105,8 @@ int main() {
     order<true>(8192 + 77, 1 << 27);
     slots<0, 1>(); slots<0, 5>(); slots<1, 2>(); slots<2, 3>(); slots<3, 4>(); slots<4, 4>(); slots<5, 5>();
     slots<6, 5>(); slots<9, 4>(); slots<8, 6>();
-    copy<9, 3, MODE_SMALL, 3, 3, 3, 3>(); copy<11, 4, MODE_SMALL, 3, 3, 4, 4>(); copy<12, 4, MODE_SMALL, 5, 4, 4, 4>();
+    copy<9, 3, MODE_SMALL, 3, 3, 3, 3>(); copy<11, 4, MODE_SMALL, 3, 3, 4, 4>(); copy<11, 4, MODE_SMALL, 3, 3, 4, 4, true>();
+    copy<12, 4, MODE_SMALL, 5, 4, 4, 4>();
     copy<13, 5, MODE_SMALL, 3, 5, 4, 4>();
     copy<14, 5, MODE_SMALL, 5, 5, 5, 4>(); copy<16, 6, MODE_SMALL, 3, 6, 5, 5>(); copy<8, 4, MODE_COLS, 3, 4, 4, 0>();
     copy<9, 5, MODE_COLS, 3, 5, 4, 0>(); copy<10, 5, MODE_COLS, 3, 5, 5, 0>();
